@@ -42,6 +42,12 @@ constexpr int32_t kMaxKPrime = 256;
 // Tail split: at most 8 pieces, and a tail region of at most 2^18 lists.
 constexpr int32_t kMaxTailParts = 8;
 constexpr int64_t kTailLists = 1 << 18;
+// X against X from this many rows on runs as one split in the grouped order
+// with its pruned scan; below, splitting the references over more workgroups
+// gains more than the order costs (about 0.1 ms).
+constexpr int64_t kPruneMinRows = 20000;
+// Smallest query block for which a shrunken plan reserves the pruned scan's boxes.
+constexpr int64_t kPruneMinBlock = 8192;
 
 tod_status resolve_options(const tod_options* in, tod_options* out) {
   tod_default_options(out);
@@ -106,6 +112,12 @@ void set_splits(Plan* p, int64_t s) {
   p->split_len = len;
 }
 
+// The pruned scan's kind and the grouped order's keys, which follow from it.
+static void set_prune(Plan* p, int32_t kind) {
+  p->prune = kind;
+  p->groups = kind == kPrunePivot ? kPivots * kRadBins : order_groups(p->nr, p->d);
+}
+
 tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, int32_t self,
                      const tod_options& o, Plan* p, const char** why) {
   *why = "";
@@ -164,7 +176,11 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   if (qb > p->nq_pad) qb = p->nq_pad;
   p->query_block = qb;
   p->blocks = (nq + qb - 1) / qb;
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits : auto_splits(qb, nr));
+  // (The pruned scan of X against X cuts its own work: one split.)
+  const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
+                      prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
+                      (nr >= kPruneMinRows || o.reorder > 0) && d > kBoxDim;
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr));
   p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
   // operand fits in registers and whose shortlist is 16, 32 or 64 long.  Rows
@@ -212,7 +228,17 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   const bool want = o.reorder > 0 || (o.reorder == 0 && nr >= kOrderMinRows);
   // (With runs, the tile scans the whole set in pieces whatever S is.)
   p->order = (self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
-  p->groups = order_groups(nr, d);
+  if (p->tile_kind == 1) {
+    const int32_t r = (int32_t)kp / p->runs / 2;
+    // (A box holds at least kUnitRows rows.)
+    p->stage_rows = 32 * mt::stage_subs(p->dpad_t, p->fold, r);
+    if (p->stage_rows < mt::kUnitRows) p->stage_rows = mt::kUnitRows;
+    p->tile_rows = 32 * mt::tile_waves(p->dpad_t, p->fold, r) *
+                   mt::query_groups(p->dpad_t, p->fold, r);
+  }
+  // Pruned scan: wherever the grouped order applies (its boxes cost 4 bytes
+  // a row and a stage test per 64 stages).
+  set_prune(p, p->order && d > kBoxDim ? kPrunePivot : kPruneNone);
   // Tail split of the register-list tile with one reference split (not with
   // runs: their pieces already halve every workgroup's scan).
   p->tail_parts = 1;
@@ -247,6 +273,12 @@ Layout make_layout(const Plan& p) {
   L.rho_q = take(sizeof(double) * (p.self ? p.nr_pad : p.nq_pad));
   L.partial = take(sizeof(uint64_t) * p.query_block * p.splits * p.kprime);
   L.ptail = take(sizeof(uint64_t) * p.tail_lists * p.kprime);
+  if (p.prune == kPrunePivot) {
+    // The rows' pivot distances lie over the partial lists (dead before the
+    // first tile launch writes a list); room beyond both regions if needed.
+    const size_t want = sizeof(float) * kPivots * (size_t)p.nr;
+    if (off - L.partial < want) (void)take(want - (off - L.partial));
+  }
   L.worklist = take(sizeof(int32_t) * p.nq);
   L.fbtau = take(sizeof(double) * p.nq);
   // Chunk lists exist only when fewer than kFbGrid rows fail, so kFbGrid
@@ -263,6 +295,17 @@ Layout make_layout(const Plan& p) {
     L.boff = take(sizeof(int32_t) * (size_t)nb * p.groups);
   } else {
     L.perm = L.lab = L.oseed = L.cstart = L.bcnt = L.boff = 0;
+  }
+  L.kstart = L.box32 = L.sbox = L.substart = L.plan = 0;
+  if (p.prune) {
+    const size_t subs = (size_t)(p.nr_pad / 32);
+    const size_t stages = (size_t)((p.nr + p.stage_rows - 1) / p.stage_rows);
+    const size_t tiles = (size_t)((p.query_block + p.tile_rows - 1) / p.tile_rows);
+    L.kstart = take(sizeof(int32_t) * (size_t)p.groups);
+    L.box32 = take(sizeof(float) * 2 * kBoxDim * subs);
+    L.sbox = take(sizeof(float) * 2 * kBoxDim * stages);
+    L.substart = take(sizeof(int32_t) * subs);
+    L.plan = take(sizeof(int32_t) * (size_t)plan_words((int64_t)tiles, kTailLists / p.tile_rows));
   }
   if (p.lists) {
     L.idx32 = take(sizeof(int32_t) * p.nq * p.k);
@@ -285,6 +328,15 @@ Layout make_layout(const Plan& p) {
 // one 32-row block fits, or when the caller fixed the query block or the
 // splits.
 tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string* why) {
+  // The pruned scan's boxes go first: the same plan without them.
+  if (p->prune) {
+    Plan q = *p;
+    set_prune(&q, kPruneNone);
+    if (make_layout(q).total <= ws_bytes) {
+      *p = q;
+      return TOD_OK;
+    }
+  }
   if (o.query_block > 0 || o.ref_splits > 0) {
     *why = "the query block or the reference splits were fixed by the caller";
     return TOD_ERR_WORKSPACE;
@@ -294,9 +346,12 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   q.tail_parts = 1;
   q.tail_auto = 0;
   q.tail_lists = 0;
-  if (make_layout(q).total <= ws_bytes) {
-    *p = q;
-    return TOD_OK;
+  for (int with_prune = q.prune ? 1 : 0; with_prune >= 0; --with_prune) {
+    if (!with_prune) set_prune(&q, kPruneNone);
+    if (make_layout(q).total <= ws_bytes) {
+      *p = q;
+      return TOD_OK;
+    }
   }
   // The grouped scan order needs buffers of its own and applies only with one
   // split; a shrunken plan may end up with one split where the one-block plan
@@ -306,17 +361,29 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   const size_t per = (size_t)q.kprime * sizeof(uint64_t);  // partial-list bytes per row and split
   const bool want = o.reorder > 0 || (o.reorder == 0 && q.nr >= kOrderMinRows);
   const bool may_order = q.self && q.tile_kind == 1 && want;
+  const int32_t prune = q.d > kBoxDim ? kPrunePivot : kPruneNone;
   size_t need = 0;
-  for (int with_order = may_order ? 1 : 0; with_order >= 0; --with_order) {
+  // (2: the order and the pruned scan, only while the block keeps
+  // kPruneMinBlock rows; 1: the order alone; 0: neither.)
+  for (int with_order = may_order ? (prune ? 2 : 1) : 0; with_order >= 0; --with_order) {
     Plan f = q;
     f.query_block = 0;  // no partial lists: the fixed part of the layout
-    f.order = with_order;
+    f.order = with_order ? 1 : 0;
+    set_prune(&f, with_order == 2 ? prune : kPruneNone);
     const size_t fixed = make_layout(f).total;
     need = fixed + 32 * per + 256;
     if (ws_bytes < need) continue;
     const size_t room = ws_bytes - fixed - 256;  // the partial region's alignment slack
     int64_t qb = (int64_t)(room / per) / 32 * 32;
     if (qb > f.nq_pad) qb = f.nq_pad;
+    if (with_order == 2) {
+      // (The plan's per-tile words come off the room; one split.)
+      qb = (int64_t)(room / (per + 1)) / 32 * 32;
+      if (qb > f.nq_pad) qb = f.nq_pad;
+      if (qb < kPruneMinBlock && qb < f.nq_pad) continue;
+      f.query_block = qb;
+      if (auto_splits(qb, f.nr) != 1 || make_layout(f).total > ws_bytes) continue;
+    }
     int64_t s = auto_splits(qb, f.nr);
     const int64_t smax = (int64_t)(room / ((size_t)qb * per));
     if (s > smax) s = smax;
@@ -324,6 +391,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
     f.blocks = (f.nq + qb - 1) / qb;
     set_splits(&f, s);
     f.order = (with_order && (f.splits == 1 || f.runs > 1)) ? 1 : 0;
+    if (!f.order) set_prune(&f, kPruneNone);
     if (make_layout(f).total > ws_bytes) {
       *why = "internal: the fitted plan does not fit";
       return TOD_ERR_INTERNAL;
@@ -527,6 +595,22 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
   a.cstart = p.order ? (int32_t*)(base + L.cstart) : nullptr;
   a.bcnt = p.order ? (int32_t*)(base + L.bcnt) : nullptr;
   a.boff = p.order ? (int32_t*)(base + L.boff) : nullptr;
+  if (p.prune) {
+    a.prune = p.prune;
+    a.stage_rows = p.stage_rows;
+    a.tile_rows = p.tile_rows;
+    a.kstart = (int32_t*)(base + L.kstart);
+    a.pdist = (float*)(base + L.partial);
+    a.box32 = (float*)(base + L.box32);
+    a.sbox = (float*)(base + L.sbox);
+    a.substart = (int32_t*)(base + L.substart);
+    // The work plan: one run, one split, pieces chosen by the planner.
+    if (p.runs == 1 && p.splits == 1 && p.tail_auto && tod::plan_extra(p) > 0) {
+      a.plan = (int32_t*)(base + L.plan);
+      a.plan_cap = tod::plan_extra(p);
+      a.plan_tiles = 1 + 2 * a.plan_cap;
+    }
+  }
   a.idx32 = p.lists ? (int32_t*)(base + L.idx32) : nullptr;
   a.d64 = p.lists ? (double*)(base + L.d64) : nullptr;
   a.lrd = lof ? (double*)(base + L.lrd) : nullptr;

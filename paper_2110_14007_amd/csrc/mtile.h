@@ -61,6 +61,11 @@ __device__ __forceinline__ f32x16 mfma(typename Frag<ET>::V a, typename Frag<ET>
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// Rows around a tile's own that the pruned scan takes before its first test of
+// the boxes.  At 10^6 rows of 64 (ten clusters) 4,096 rows give every query a
+// threshold that rules the other clusters out: 47 ms against 60 with 512.
+constexpr int kHomeRows = 4096;
+
 constexpr int kMerge = 16;  // queue entries one merge takes per lane
 
 // Queue slots per lane.  16-entry lists see few insertions: a 16-slot queue
@@ -296,10 +301,6 @@ struct Layout {
   // group hit distinct banks.
   static constexpr int rowb = DPAD == 16 ? 32 : DPAD * 2 + 16;
   static constexpr int cpr = DPAD / 8;  // 16-byte chunks per row
-  // Sub-tiles per stage: the stage pair, seeds and four queues stay under
-  // 80 KiB so that at least two workgroups share a CU.  (Folded rows with
-  // 16-entry lists take stages of four: see launch_mtile.)
-  static constexpr int ns = DPAD == 16 ? 8 : (DPAD == 32 ? 4 : (DPAD == 64 ? 2 : 1));
   // Rows of 256 or more elements keep a 32-query operand of DPAD/2 VGPRs
   // per lane: such kernels run one wave per SIMD.
   static constexpr bool wide = DPAD >= 256;
@@ -319,27 +320,18 @@ __host__ __device__ constexpr int stage_buffers(int dpad, bool fold, int nq) {
   return dpad >= 512 && !fold && nq == 1 ? 3 : 2;
 }
 
-// Query columns per wave: 64 (two 32-query groups sharing every A fragment)
-// for rows of 512 elements with lists of up to 32 entries, whose 32-step MFMA
-// chains otherwise need one LDS fragment per MFMA; 32 otherwise.  The two
-// groups' operands take all 256 AGPRs; 64-entry lists for two groups (128
-// VGPRs) then leave the compiler too few registers, and it spills part of
-// the operand to scratch memory.
-__host__ __device__ constexpr int query_groups(int dpad, bool fold, int r) {
-  return dpad >= 512 && !fold && r <= 16 ? 2 : 1;
-}
-
 // Queue slots per lane and query group (two groups: 16 slots, the LDS of two
 // 28-slot queues per wave does not fit beside the stages).
 template <int R, int NQ>
 constexpr int queue_slots() { return NQ == 1 ? queue_cap<R>() : 16; }
 
-// Stage buffers, their seeds and the queues.
+// Stage buffers, their seeds, the queues and the pruned scan's stage masks.
 __host__ __device__ constexpr size_t lds_bytes(int dpad, bool fold, int w, int ns, int qcap,
                                                int nq) {
   return (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * (dpad == 16 ? 32 : dpad * 2 + 16) +
          (fold ? 0 : (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * sizeof(uint2)) +
-         (size_t)w * nq * qcap * 64 * sizeof(uint2);
+         (size_t)w * nq * qcap * 64 * sizeof(uint2) +
+         (dpad == 16 ? 0 : (size_t)2 * w * sizeof(uint64_t));
 }
 
 // At least two waves per SIMD for lists of up to 32 entries and rows of up to
@@ -356,7 +348,10 @@ __host__ __device__ constexpr int min_waves() {
   return R >= 32 || DPAD >= 256 ? 1 : (DPAD == 16 && R <= 8 ? (FOLD ? 4 : 3) : 2);
 }
 
-template <typename ET, int DPAD, bool FOLD, int R, int W, int NS, int NG, int NQ>
+// PR: the pruned scan (its stage sequence is data dependent; the plain scan's
+// loop is kept apart, because carrying the sequence through it cost rows of 65
+// to 128 elements, whose stages are one sub-tile, 10%).
+template <typename ET, int DPAD, bool FOLD, int R, int W, int NS, int NG, int NQ, bool PR>
 __global__ void __launch_bounds__(W * 64)
     __attribute__((amdgpu_waves_per_eu(min_waves<DPAD, FOLD, R>())))
 mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
@@ -387,17 +382,41 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int h = lane >> 5, col = lane & 31;
   if (a.ctrl->nonfinite) return;  // uniform over the grid
+  // The work plan decides which of the two scans runs (uniform over the grid).
+  if (a.plan && (a.plan[0] >= 0) != PR) return;
   // This lane's queue of query group u: qbase + ((wave NQ + u) kQCap + i) 64 + lane.
   uint2* const myq0 = qbase + wave * NQ * kQCap * 64 + lane;
 
+  // The workgroup's tile of queries and, where its scan is cut, its piece of
+  // the scan order: blockIdx.y with the tail split or runs (a.parts > 1);
+  // with a work plan, one workgroup per tile and per extra piece of the plan.
+  // (The extra pieces come first, then the tiles from the last one on: the
+  // grouped order puts the rows far from their group, whose scans are the
+  // longest, at the end.)
+  int tile = blockIdx.x, piece = blockIdx.y, parts = a.parts;
+  int extra = -1;  // with a plan: the extra piece (its list's place)
+  if (PR && a.plan) {
+    const int tiles = (int)((q_rows + W * 32 * NQ - 1) / (W * 32 * NQ));
+    const int extras = a.plan[0];
+    if (tile < extras) {
+      extra = tile;
+      tile = a.plan[1 + 2 * extra];
+      piece = a.plan[2 + 2 * extra];
+    } else {
+      tile = tiles - 1 - (tile - extras);
+      piece = 0;
+      if (tile < 0) return;  // uniform per workgroup
+    }
+    tile = __builtin_amdgcn_readfirstlane(tile);
+    piece = __builtin_amdgcn_readfirstlane(piece);
+    parts = __builtin_amdgcn_readfirstlane(1 + a.plan[a.plan_tiles + 3 * tile + 1]);
+  }
   // The wave's queries: NQ groups of 32 from q0 on (group u: q0 + 32 u ..).
-  const int64_t group = (int64_t)blockIdx.x * W + wave;
+  const int64_t group = (int64_t)tile * W + wave;
   const bool active = group * 32 * NQ < q_rows;  // uniform per wave
   const int64_t q0 = q_begin + group * 32 * NQ;
-  // blockIdx.y: the reference split, or with the tail split (a.parts > 1,
-  // one split) the piece of the scan order this workgroup takes.
-  const int split = blockIdx.y;
-  const bool pieces = a.parts > 1;
+  const int split = piece;  // reference split (no pieces)
+  const bool pieces = parts > 1 || (PR && a.plan);
   const int64_t r_begin = pieces ? 0 : (int64_t)split * a.split_len;
   const int64_t r_end = r_begin + a.split_len < a.nr ? r_begin + a.split_len : a.nr;
   const int64_t r_end32 = (r_end + 31) & ~(int64_t)31;  // rows < r_end32 exist (padded copy)
@@ -833,37 +852,175 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // workgroup starts at the stage holding the first row of the group of its
   // first query and wraps around; concurrent workgroups mostly share a group,
   // and so the stream they read.  Otherwise the split is scanned in order.
-  const int nst = (int)((r_end - r_begin + TR - 1) / TR);
-  int st0 = 0;
-  if (a.cstart) {
-    // The last group starting at or before p0 (starts ascend; an empty group
-    // shares its start with the next one).
-    const int p0 = (int)(q_begin + (int64_t)blockIdx.x * (W * 32 * NQ));
-    int lo = 0, hi = a.groups;  // cstart[lo] <= p0 < cstart[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (a.cstart[mid] <= p0) lo = mid;
-      else hi = mid;
+  // With the pruned scan the stages around the workgroup's own rows come
+  // first (they give every query a threshold near its final one); the rest
+  // follow from the start of the rows' group on, wrapping round.  A cut scan's
+  // piece takes every parts-th unit of that order (without the boxes,
+  // contiguous pieces of it).  The pruned scan's unit is the box: a stage, or
+  // as many as make up 128 rows.
+  constexpr int UR = PR && TR < kUnitRows ? kUnitRows : TR;  // rows of a unit
+  const int nst = (int)((r_end - r_begin + UR - 1) / UR);
+  const int64_t p0 = q_begin + (int64_t)tile * (W * 32 * NQ);  // the tile's first query
+  int st0 = 0, hs = 0, hn = 0;  // first stage of the rest; home stages [hs, hs + hn)
+  int nscan = nst, stepi = 1, offi = 0;
+  if constexpr (PR) {
+    const int own = (int)(p0 / UR);
+    constexpr int kHome = kHomeRows / UR;
+    static_assert(kHome <= 64, "the home units are one chunk");
+    hn = kHome < nst ? kHome : nst;
+    hs = own - hn / 2;
+    hs = hs < 0 ? 0 : (hs + hn <= nst ? hs : nst - hn);
+    st0 = a.substart[p0 >> 5] / UR;
+    if (st0 >= hs && st0 < hs + hn) st0 = hs + hn < nst ? hs + hn : 0;
+    stepi = parts;
+    offi = pieces ? piece : 0;
+    nscan = (nst - offi + stepi - 1) / stepi;
+  } else {
+    if (a.cstart) {
+      // The last group starting at or before p0 (starts ascend; an empty group
+      // shares its start with the next one).
+      if (a.substart) {
+        st0 = a.substart[p0 >> 5] / TR;
+      } else {
+        int lo = 0, hi = a.groups;  // cstart[lo] <= p0 < cstart[hi]
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (a.cstart[mid] <= p0) lo = mid;
+          else hi = mid;
+        }
+        st0 = (int)((a.cstart[lo] - r_begin) / TR);
+      }
     }
-    st0 = (int)((a.cstart[lo] - r_begin) / TR);
-  }
-  // Tail split: piece `split` of `parts` takes the stages [ib, ib + nscan) of
-  // the scan order.
-  int nscan = nst;
-  if (pieces) {
-    // (64-bit products: up to 128 pieces with two runs of 64 splits.)
-    const int ib = (int)((int64_t)split * nst / a.parts);
-    nscan = (int)((int64_t)(split + 1) * nst / a.parts) - ib;
-    st0 += ib;
-    st0 = st0 >= nst ? st0 - nst : st0;
+    // Tail split: piece `split` of `parts` takes the stages [ib, ib + nscan) of
+    // the scan order.
+    if (pieces) {
+      // (64-bit products: up to 128 pieces with two runs of 64 splits.)
+      const int ib = (int)((int64_t)split * nst / parts);
+      nscan = (int)((int64_t)(split + 1) * nst / parts) - ib;
+      st0 += ib;
+      st0 = st0 >= nst ? st0 - nst : st0;
+    }
   }
   // First row of the i-th stage scanned (i < nscan + 2 <= nst + 2; stages past
   // the last one wrap round and are loaded but never read).
-  auto t_of = [&](int i) -> int64_t {
+  [[maybe_unused]] auto t_of = [&](int i) -> int64_t {
     int s = st0 + i;
     s = s >= nst ? s - nst : s;
     s = s >= nst ? s - nst : s;
     return r_begin + (int64_t)s * TR;
+  };
+
+  // Pruned scan: unit of the i-th scan position.
+  [[maybe_unused]] auto unit_at = [&](int i) -> int {
+    i = i * stepi + offi;
+    if (i < hn) return hs + i;
+    i -= hn;
+    // The home units lie `skip` units past st0 in wrapping order: left out.
+    int skip = hs - st0;
+    skip = skip < 0 ? skip + nst : skip;
+    i += i >= skip ? hn : 0;
+    int s = st0 + i;
+    return s >= nst ? s - nst : s;
+  };
+  // The pruned scan as a sequence of stages: next() gives the next stage's
+  // first row, or -1 at the end, and `need`, whether this wave's queries need
+  // it.  64 scan positions at a time, lane l bounds the distance between the
+  // wave's query box and the box of the unit at position l from below; a unit
+  // survives if the bound does not exceed the distance its K'-th entry implies
+  // for some query of the wave.  Exactness: a skipped row's quantised squared
+  // distance D is then at least N_i + key of the query's K'-th entry, so its
+  // exact key D - N_i is no smaller than the final list's last key, which is
+  // what the certificate asks of every row left out.  The margin 2^-16 covers
+  // the rounding of the bound (at most 16 fp32 terms; the boxes are widened
+  // where they are rounded).  The workgroup stages what any wave needs.
+  // (Scalar values throughout: in vector registers the stage addresses and the
+  // per-stage tests cost rows of 65 to 128 elements a fifth of their time.)
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  st0 = uniform(st0);
+  hs = uniform(hs);
+  uint64_t um = 0, om = 0;  // units of the chunk: any wave's, this wave's
+  int cb = 0, cn = 0, par = 0;
+  [[maybe_unused]] int64_t ucur = -1, uend = 0;
+  [[maybe_unused]] bool uneed = false;
+  uint64_t* const wneed = (uint64_t*)(qbase + W * NQ * kQCap * 64);  // [2][W]
+  [[maybe_unused]] auto next = [&](bool& need) __attribute__((always_inline)) -> int64_t {
+    if constexpr (UR > TR) {
+      // The other stages of the unit.
+      if (ucur >= 0 && ucur + TR < uend) {
+        ucur += TR;
+        need = uneed;
+        return ucur;
+      }
+    }
+    while (!um) {
+      cb += cn;
+      if (cb >= nscan) {
+        need = false;
+        ucur = -1;
+        return -1;
+      }
+      // (The home stages fill the lists before the first test.)
+      cn = cb == 0 ? (hn + stepi - 1) / stepi : 64;
+      if (cn > nscan - cb) cn = nscan - cb;
+      // Largest squared distance any of the wave's lists still admits.
+      float lim = -INFINITY;
+      if (active) {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+          const int64_t q = q0 + 32 * u + col;
+          if (group * 32 * NQ + 32 * u + col < q_rows) {
+            const double dq = a.n64_q[q] - 2.0 * (double)thr[u];
+            lim = fmaxf(lim, (float)dq);
+          }
+        }
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) lim = fmaxf(lim, __shfl_xor(lim, off, 64));
+      lim = fmaxf(lim, 0.0f) * (1.0f + 0x1p-16f);
+      bool ok = false;
+      if (active && lane < cn) {
+        const float4* bx =
+            reinterpret_cast<const float4*>(a.sbox + (int64_t)unit_at(cb + lane) * (2 * kBoxDim));
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+          // (Uniform address: the query box comes through the scalar cache.)
+          const int64_t sq = (q0 >> 5) + u;
+          const float* qb = a.box32 + (int64_t)__builtin_amdgcn_readfirstlane((int)sq) * (2 * kBoxDim);
+          if (group * 32 * NQ + 32 * u >= q_rows) continue;
+          float lb = 0.0f;
+#pragma unroll
+          for (int t = 0; t < kBoxDim / 4; ++t) {
+            const float4 lo = bx[t], hi = bx[kBoxDim / 4 + t];
+            const float g0 = max3f(lo.x - qb[kBoxDim + 4 * t], qb[4 * t] - hi.x, 0.0f);
+            const float g1 = max3f(lo.y - qb[kBoxDim + 4 * t + 1], qb[4 * t + 1] - hi.y, 0.0f);
+            const float g2 = max3f(lo.z - qb[kBoxDim + 4 * t + 2], qb[4 * t + 2] - hi.z, 0.0f);
+            const float g3 = max3f(lo.w - qb[kBoxDim + 4 * t + 3], qb[4 * t + 3] - hi.w, 0.0f);
+            if (a.prune == kPrunePivot) {
+              lb = fmaxf(fmaxf(lb, g0), fmaxf(fmaxf(g1, g2), g3));
+            } else {
+              lb += g0 * g0 + g1 * g1 + g2 * g2 + g3 * g3;
+            }
+          }
+          if (a.prune == kPrunePivot) lb *= lb;
+          ok = ok || !(lb > lim);
+        }
+      }
+      om = __ballot(ok);
+      if (lane == 0) wneed[par * W + wave] = om;
+      stage_barrier();
+#pragma unroll
+      for (int w = 0; w < W; ++w) um |= wneed[par * W + w];
+      um = ((uint64_t)__builtin_amdgcn_readfirstlane((int)(um >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)um);
+      par ^= 1;
+    }
+    const int bit = __builtin_ctzll(um);
+    need = (om >> bit) & 1;
+    um &= um - 1;
+    ucur = r_begin + (int64_t)uniform(unit_at(cb + bit)) * UR;
+    uneed = need;
+    uend = ucur + UR < r_end ? ucur + UR : r_end;
+    return ucur;
   };
 
   if constexpr (DL) {
@@ -883,22 +1040,58 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     // The seeds of stage (tn, bn) are loaded first (two lanes: a branch, kept
     // out of the chain); a stage body issues the rows inside its chain, and a
     // wave with no queries has no chain and issues them itself.
-    auto dl_body = [&](int64_t t0, int b, int64_t tn, int bn) __attribute__((always_inline)) {
+    auto dl_body = [&](int64_t t0, int b, int64_t tn, int bn, bool need)
+        __attribute__((always_inline)) {
       dl_t0 = tn;
       dl_b = bn;
       dl_row(TR / W);
-      if (active) stage_body(t0, b);
+      if (active && need) stage_body(t0, b);
       else
 #pragma unroll
         for (int i = 0; i < TR / W; ++i) dl_row(i);
     };
+    // (Past the end the pipeline loads the first stage again; nothing reads it.)
+    if constexpr (PR) {
+    [[maybe_unused]] bool n0, n1, n2;
+    int64_t t0 = next(n0);
+    const int64_t td = t0 < 0 ? r_begin : t0;
+    if constexpr (NBUF == 3) {
+      int64_t t1 = next(n1);
+      dl_issue(td, 0);
+      dl_issue(t1 < 0 ? td : t1, 1);
+      dl_barrier<kDlRows>();
+      for (int b = 0; t0 >= 0;) {
+        // Buffer (b + 2) % 3 was last read in the previous trip, before its barrier.
+        const int64_t t2 = next(n2);
+        const int b2 = b == 0 ? 2 : b - 1;
+        dl_body(t0, b, t2 < 0 ? td : t2, b2, n0);
+        dl_barrier<kDlRows>();
+        t0 = t1;
+        n0 = n1;
+        t1 = t2;
+        n1 = n2;
+        b = b == 2 ? 0 : b + 1;
+      }
+    } else {
+      dl_issue(td, 0);
+      dl_barrier<0>();
+      for (int b = 0; t0 >= 0; b ^= 1) {
+        // Buffer b ^ 1 was last read in the previous trip, before its barrier.
+        const int64_t t1 = next(n1);
+        dl_body(t0, b, t1 < 0 ? td : t1, b ^ 1, n0);
+        dl_barrier<0>();
+        t0 = t1;
+        n0 = n1;
+      }
+    }
+    } else {
     if constexpr (NBUF == 3) {
       dl_issue(t_of(0), 0);
       dl_issue(t_of(1), 1);
       dl_barrier<kDlRows>();
       for (int it = 0; it < nscan; ++it) {
         // Buffer (it + 2) % 3 was last read in trip it - 1, before its barrier.
-        dl_body(t_of(it), it % 3, t_of(it + 2), (it + 2) % 3);
+        dl_body(t_of(it), it % 3, t_of(it + 2), (it + 2) % 3, true);
         dl_barrier<kDlRows>();
       }
     } else {
@@ -906,13 +1099,57 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       dl_barrier<0>();
       for (int it = 0; it < nscan; ++it) {
         // Buffer (it + 1) & 1 was last read in trip it - 1, before its barrier.
-        dl_body(t_of(it), it & 1, t_of(it + 1), (it + 1) & 1);
+        dl_body(t_of(it), it & 1, t_of(it + 1), (it + 1) & 1, true);
         dl_barrier<0>();
       }
+    }
     }
     // No staging write may outlive the workgroup's LDS allocation.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
+  if constexpr (PR) {
+  [[maybe_unused]] bool n0, n1, n2;
+  int64_t t0 = next(n0);
+  const int64_t td = t0 < 0 ? r_begin : t0;
+  TOD_MT_FETCH(td, st, sth)
+  TOD_MT_PUT(0, st, sth)
+  if constexpr (PF2) {
+    // Two stages per trip: each register set has a fixed role in straight-line
+    // code, so every wait is for the older set only, and the stage barrier
+    // (no release fence) leaves the newer set's loads in flight.
+    int64_t t1 = next(n1);
+    TOD_MT_FETCH((t1 < 0 ? td : t1), su, suh)
+    stage_barrier();
+    for (; t0 >= 0;) {
+      int64_t t2 = next(n2);
+      TOD_MT_FETCH((t2 < 0 ? td : t2), st, sth)
+      if (n0) stage_body(t0, 0);
+      TOD_MT_PUT(1, su, suh)
+      stage_barrier();
+      t0 = t2;
+      n0 = n2;
+      if (t1 < 0) break;
+      t2 = next(n2);
+      TOD_MT_FETCH((t2 < 0 ? td : t2), su, suh)
+      if (n1) stage_body(t1, 1);
+      TOD_MT_PUT(0, st, sth)
+      stage_barrier();
+      t1 = t2;
+      n1 = n2;
+    }
+  } else {
+    __syncthreads();
+    for (int b = 0; t0 >= 0; b ^= 1) {
+      const int64_t t1 = next(n1);
+      TOD_MT_FETCH((t1 < 0 ? td : t1), st, sth)
+      if (n0) stage_body(t0, b);
+      TOD_MT_PUT(b ^ 1, st, sth)
+      __syncthreads();
+      t0 = t1;
+      n0 = n1;
+    }
+  }
+    } else {
   TOD_MT_FETCH(t_of(0), st, sth)
   TOD_MT_PUT(0, st, sth)
   if constexpr (PF2) {
@@ -942,6 +1179,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       __syncthreads();
     }
   }
+    }
   }
 #undef TOD_MT_FETCH
 #undef TOD_MT_PUT
@@ -952,7 +1190,12 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       const int64_t ql = group * 32 * NQ + 32 * u + col;
       if (ql < q_rows) {
         uint64_t* dst =
-            a.partial + (ql * (pieces ? a.parts : a.splits) + split) * (2 * R) + h * R;
+            (extra >= 0 ? a.ptail + ((int64_t)extra * (W * 32 * NQ) +
+                                     (ql - (int64_t)tile * (W * 32 * NQ))) * (2 * R)
+             : PR && a.plan
+                 ? a.partial + ql * (2 * R)
+                 : a.partial + (ql * (pieces ? parts : a.splits) + split) * (2 * R)) +
+            h * R;
 #pragma unroll
         for (int i = 0; i < R; ++i) {
           const uint64_t e = L[u][i];
@@ -984,16 +1227,15 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
 // With one reference split, those workgroups' scans are cut into P pieces on
 // P times as many workgroups (tail_pieces picks P), in a second launch whose
 // lists go to the tail region.
-template <typename ET, int DPAD, bool FOLD, int R,
-          int W = (FOLD && R <= 8 ? 16 : (DPAD == 64 && !FOLD && R == 16) ? 8 : 4),
-          int NS = (FOLD && R <= 8 ? 16 : (DPAD == 64 && !FOLD && R == 16) ? 4 : Layout<DPAD, FOLD>::ns),
+template <typename ET, int DPAD, bool FOLD, int R, bool PR, int W = tile_waves(DPAD, FOLD, R),
+          int NS = stage_subs(DPAD, FOLD, R),
           int NG = (DPAD <= 32 ? 4 : (DPAD == 64 ? 2 : 1)), int NQ = query_groups(DPAD, FOLD, R)>
-hipError_t launch_mtile(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
+hipError_t launch_mtile_pr(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
                         hipStream_t st, TileTail* tail) {
   const size_t lds = lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ);
   static_assert(lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ) <= 160 * 1024,
                 "LDS per workgroup");
-  const auto kern = mtile_kernel<ET, DPAD, FOLD, R, W, NS, NG, NQ>;
+  const auto kern = mtile_kernel<ET, DPAD, FOLD, R, W, NS, NG, NQ, PR>;
   constexpr int QW = W * 32 * NQ;  // queries per workgroup
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)kern,
@@ -1017,25 +1259,34 @@ hipError_t launch_mtile(const Plan& p, const Args& a, int64_t q_begin, int64_t q
     }
     return hipGetLastError();
   }
+  int dev = 0, cus = 0, per = 0;
+  const bool occ =
+      ((p.splits == 1 && p.tail_parts > 1 && a.ptail) || a.plan) &&
+      hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)kern, W * 64, lds) ==
+          hipSuccess &&
+      cus > 0 && per > 0;
+  if (!occ) (void)hipGetLastError();  // no occupancy figures: no tail split
+  if (PR && a.plan) {
+    const hipError_t e = launch_plan(p, a, q_begin, q_rows, occ ? cus * per : 256, occ ? cus : 256,
+                                     st);
+    if (e != hipSuccess) return e;
+    // Planned pieces: the tiles, then as many workgroups as there is room for
+    // extra pieces (those past the plan's count leave at once).
+    hipLaunchKernelGGL(kern, dim3((unsigned)(wgs + a.plan_cap)), dim3(W * 64), lds, st, a, q_begin,
+                       q_rows);
+    return hipGetLastError();
+  }
   int64_t main_wgs = wgs;
   int parts = 1;
-  if (p.splits == 1 && p.tail_parts > 1 && a.ptail) {
-    int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, (const void*)kern, W * 64, lds) ==
-            hipSuccess &&
-        cus > 0 && per > 0) {
-      const int64_t slots = (int64_t)cus * per;
-      const int64_t tw = wgs % slots;
-      const int64_t trows = q_rows - (wgs - tw) * QW;
-      const int64_t nst = (a.nr + 32 * NS - 1) / (32 * NS);
-      parts = tail_pieces(tw, slots, cus, p.tail_parts, p.tail_auto != 0, nst, p.tail_lists,
-                          trows);
-      if (parts > 1) main_wgs = wgs - tw;
-    } else {
-      (void)hipGetLastError();  // no occupancy figures: no tail split
-    }
+  if (occ) {
+    const int64_t slots = (int64_t)cus * per;
+    const int64_t tw = wgs % slots;
+    const int64_t trows = q_rows - (wgs - tw) * QW;
+    const int64_t nst = (a.nr + 32 * NS - 1) / (32 * NS);
+    parts = tail_pieces(tw, slots, cus, p.tail_parts, p.tail_auto != 0, nst, p.tail_lists, trows);
+    if (parts > 1) main_wgs = wgs - tw;
   }
   const int64_t main_rows = main_wgs * QW < q_rows ? main_wgs * QW : q_rows;
   if (main_wgs > 0) {
@@ -1055,6 +1306,19 @@ hipError_t launch_mtile(const Plan& p, const Args& a, int64_t q_begin, int64_t q
   hipLaunchKernelGGL(kern, dim3((unsigned)(wgs - main_wgs), (unsigned)parts), dim3(W * 64), lds,
                      st, b, q_begin + main_rows, q_rows - main_rows);
   return hipGetLastError();
+}
+
+template <typename ET, int DPAD, bool FOLD, int R>
+hipError_t launch_mtile(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
+                        hipStream_t st, TileTail* tail) {
+  if constexpr (DPAD > 16)
+    if (a.prune) {
+      const hipError_t e =
+          launch_mtile_pr<ET, DPAD, FOLD, R, true>(p, a, q_begin, q_rows, st, tail);
+      // With a plan, the plain scan follows: the plan lets one of the two run.
+      if (e != hipSuccess || !a.plan) return e;
+    }
+  return launch_mtile_pr<ET, DPAD, FOLD, R, false>(p, a, q_begin, q_rows, st, tail);
 }
 
 template <typename ET, int DPAD, bool FOLD>

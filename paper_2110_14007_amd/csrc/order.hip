@@ -9,6 +9,13 @@
 // and the filter's thresholds tighten early.  The exact kNN set of every row
 // does not depend on the order: the recheck maps positions back to input rows
 // before it ranks and writes anything.
+//
+// Pruned scan.  On clustered rows most of the references cannot be among a
+// query's nearest: the boxes of sub-tiles and stages (distances to the seeds,
+// then called pivots) bound the distance between a wave's queries and a stage
+// from below, and the tile (mtile.h) skips what lies beyond the wave's worst
+// list entry.  At 10^6 rows of 64 in ten clusters the tile's 16 launches take 50
+// ms instead of 165, at 10^5 of 32 in five 1.2 instead of 2.2.
 #include "tod_internal.h"
 
 namespace tod {
@@ -98,6 +105,130 @@ assign_kernel(const float* __restrict__ x, int64_t n, int d, int32_t* __restrict
   lab[row] = best;
 }
 
+// The pivots: kPivots of up to kSeedSamples evenly spaced rows (as many as fit
+// in LDS), the first one given, each next one drawn with probability
+// proportional to its squared distance from the nearest pivot so far
+// (k-means++ seeding, with a fixed low-discrepancy sequence in place of random
+// numbers).  Rows at random would leave some of ten clusters without a pivot in
+// four runs of five, and stages of two such clusters can hardly be told apart:
+// at 10^6 rows of 64 the tile took 65 to 85 ms from seed to seed, against 47.
+// One workgroup, bound by the latency of its kPivots dependent rounds: the
+// samples sit in LDS (read from global memory in every round it took 80 us).
+constexpr int kSeedSamples = 512;
+constexpr int kSeedThreads = 1024;
+constexpr int kSeedFloats = 36 * 1024;  // LDS for the samples
+
+int seed_samples(int64_t n, int d) {
+  int64_t m = kSeedFloats / (d + 1);
+  m = m < kSeedSamples ? m : kSeedSamples;
+  return (int)(m < n ? m : n);
+}
+
+__global__ void __launch_bounds__(kSeedThreads)
+pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
+                  const Ctrl* __restrict__ ctrl, int scale_exp, int32_t* __restrict__ srow) {
+  extern __shared__ float smp[];  // [m][d + 1], scaled
+  __shared__ float wsum[kSeedThreads / 64];
+  __shared__ int pick;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
+  for (int e = tid; e < m * d; e += kSeedThreads) {
+    const int i = e / d, t = e - i * d;
+    smp[i * (d + 1) + t] = x[((int64_t)i * n / m) * d + t] * sc;
+  }
+  if (tid == 0) pick = m - 1;
+  __syncthreads();
+  const int i = tid / tps, sub = tid & (tps - 1);  // sample, one of its tps threads
+  const float* in = smp + (i < m ? i : 0) * (d + 1);
+  float near = INFINITY;
+  int p = 0;
+  for (int c = 0; c < kPivots; ++c) {
+    if (tid == 0) srow[c] = (int32_t)((int64_t)p * n / m);
+    const float* pv = smp + p * (d + 1);
+    float acc = 0.0f;
+#pragma unroll 8
+    for (int t = sub; t < d; t += tps) {
+      const float df = in[t] - pv[t];
+      acc = fmaf(df, df, acc);
+    }
+    for (int off = 1; off < tps; off <<= 1) acc += __shfl_xor(acc, off, 64);
+    near = fminf(near, acc);
+    // Inclusive sums of the weights in sample order.
+    float incl = i < m && sub == 0 ? near : 0.0f;
+    for (int off = 1; off < 64; off <<= 1) {
+      const float o = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    float before = 0.0f, total = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kSeedThreads / 64; ++w) {
+      before += w < wave ? wsum[w] : 0.0f;
+      total += wsum[w];
+    }
+    const float u = (float)(c + 1) * 0.61803399f;
+    // (One atomic a wave: its first sample at or past the mark.)
+    const uint64_t at = __ballot(i < m && before + incl >= (u - floorf(u)) * total);
+    if (at && lane == __builtin_ctzll(at)) atomicMin(&pick, i);
+    __syncthreads();
+    p = pick;
+    __syncthreads();  // every thread has read pick before it is reset
+    if (tid == 0) pick = m - 1;
+  }
+}
+
+// Longer rows with the pruned scan: groups by the nearest pivot.  Per row the
+// scaled distances s |x - seed_c| (s the quantisation's power of two, so that
+// they neither overflow nor underflow) go to pdist, and lab = 64 c + bin of
+// the nearest seed c, bin by half octaves of the squared distance: the rows of
+// a group are laid out by their distance from its seed, so that rows far from
+// every seed (outliers, clusters without a seed) do not widen the boxes of the
+// group's bulk.
+__global__ void __launch_bounds__(kAssignThreads)
+assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d, const Ctrl* __restrict__ ctrl,
+                    int scale_exp, const int32_t* __restrict__ srow, float* __restrict__ pdist,
+                    int32_t* __restrict__ lab) {
+  extern __shared__ float seeds[];  // [kPivots][d]
+  for (int i = threadIdx.x; i < kPivots * d; i += blockDim.x) {
+    const int c = i / d, t = i - c * d;
+    seeds[i] = x[(int64_t)srow[c] * d + t];
+  }
+  __syncthreads();
+  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= n) return;
+  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
+  float acc[kPivots];
+#pragma unroll
+  for (int c = 0; c < kPivots; ++c) acc[c] = 0.0f;
+  const float* in = x + row * d;
+  for (int t = 0; t < d; ++t) {
+    const float v = in[t];
+#pragma unroll
+    for (int c = 0; c < kPivots; ++c) {
+      const float df = (v - seeds[c * d + t]) * sc;
+      acc[c] = fmaf(df, df, acc[c]);
+    }
+  }
+  int best = 0;
+  float bd = acc[0];
+#pragma unroll
+  for (int c = 1; c < kPivots; ++c) {
+    best = acc[c] < bd ? c : best;
+    bd = acc[c] < bd ? acc[c] : bd;
+  }
+  // |s (x - seed)| < 2^(E+1) in every column: D^2 < 4 d 4^E.
+  const int top = (int)(__float_as_uint(ldexpf((float)d, 2 * scale_exp + 2)) >> 22);
+  int bin = (int)(__float_as_uint(bd) >> 22) - top + (kRadBins - 1);
+  bin = bin < 0 ? 0 : (bin > kRadBins - 1 ? kRadBins - 1 : bin);
+  lab[row] = best * kRadBins + bin;
+  float4* out = reinterpret_cast<float4*>(pdist + row * kPivots);
+#pragma unroll
+  for (int c = 0; c < kPivots / 4; ++c)
+    out[c] = make_float4(sqrtf(acc[4 * c]), sqrtf(acc[4 * c + 1]), sqrtf(acc[4 * c + 2]),
+                         sqrtf(acc[4 * c + 3]));
+}
+
 // Rows per group in each block of kOrdRows rows.
 __global__ void __launch_bounds__(256)
 count_kernel(const int32_t* __restrict__ lab, int64_t n, int G, int32_t* __restrict__ bcnt) {
@@ -156,6 +287,37 @@ group_starts_kernel(int G, int32_t* __restrict__ cstart) {
   if (lane == 0) cstart[0] = 0;
 }
 
+// Key starts of the pivot order: one wave per seed group, lane = distance bin.
+// Bins more than four half octaves above the group's median bin (rows more
+// than twice as far from the seed as the median row) form the group's far
+// class.  Layout: the near classes group by group, then the far classes; within
+// a class by bin.  start[key] replaces the key's total; kstart[key] is the
+// start of the key's class.
+__global__ void __launch_bounds__(kPivots * kRadBins)
+pivot_starts_kernel(int32_t* __restrict__ start, int32_t* __restrict__ kstart) {
+  __shared__ int32_t tot[2][kPivots];
+  const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int32_t v = start[threadIdx.x + 1];
+  __syncthreads();  // every total is read before a start overwrites it
+  const int32_t incl = wave_incl_sum(v, lane);
+  const int32_t all = __shfl(incl, 63, 64);
+  const uint64_t past = __ballot(2 * (int64_t)incl >= all);
+  const int cut = __builtin_ctzll(past) + 4;  // lane 63's sum is `all`: past is never 0
+  const int32_t near = __shfl(incl, cut < 63 ? cut : 63, 64);
+  if (lane == 0) {
+    tot[0][g] = near;
+    tot[1][g] = all - near;
+  }
+  __syncthreads();
+  int32_t at = 0;
+  const bool far = lane > cut;
+  for (int i = 0; i < kPivots; ++i) at += (far || i < g) ? tot[0][i] : 0;
+  if (far)
+    for (int i = 0; i < g; ++i) at += tot[1][i];
+  kstart[threadIdx.x] = at;
+  start[threadIdx.x] = at + incl - v - (far ? near : 0);
+}
+
 // perm[position] = row, stable within each group: one wave per block walks
 // its rows 64 at a time; each lane counts the lanes of the same group below
 // it (its rank) and in all (the group's count in these 64 rows), writes its
@@ -163,7 +325,7 @@ group_starts_kernel(int G, int32_t* __restrict__ cstart) {
 // advances the group's next position.  (A group's next position starts at
 // the group's start plus the block's offset within the group.)
 __global__ void __launch_bounds__(64)
-scatter_kernel(const int32_t* __restrict__ lab, int64_t n, int G,
+scatter_kernel(const int32_t* __restrict__ lab, int64_t n, int G, int bits,
                const int32_t* __restrict__ boff, const int32_t* __restrict__ cstart,
                int32_t* __restrict__ perm) {
   __shared__ int32_t next[kOrdMaxC];
@@ -175,17 +337,289 @@ scatter_kernel(const int32_t* __restrict__ lab, int64_t n, int G,
   for (int64_t r = r0; r < r1; r += 64) {
     const int64_t row = r + lane;
     const int l = row < r1 ? lab[row] : -1;
-    int rank = 0, cnt = 0;
-    for (int j = 0; j < 64; ++j) {
-      const bool eq = __shfl(l, j, 64) == l;
-      cnt += eq ? 1 : 0;
-      rank += (eq && j < lane) ? 1 : 0;
+    // Lanes of the same group: one ballot per bit of the group number.
+    uint64_t same = __ballot(l >= 0);
+    for (int b = 0; b < bits; ++b) {
+      const uint64_t m = __ballot((l >> b) & 1);
+      same &= ((l >> b) & 1) ? m : ~m;
     }
+    const int cnt = __popcll(same);
+    const int rank = __popcll(same & ((1ull << lane) - 1));
     if (l >= 0) perm[next[l] + rank] = (int32_t)row;
     __syncthreads();  // every lane has read next[] before it moves
     if (l >= 0 && rank == 0) next[l] += cnt;
     __syncthreads();
   }
+}
+
+// ---------------------------------------------------------------------------
+// Boxes and the work plan of the pruned scan.
+// ---------------------------------------------------------------------------
+constexpr int kSubsPerBlock = 16;
+
+// Pivot boxes of the 32-row sub-tiles: one thread per (sub-tile, pivot).  The
+// quantised rows' distances differ from the rows' own by at most the two
+// radii (<= 2 P): every box is widened by P.  eps covers the fp32 rounding of
+// the distances; the absolute 2^-6 (rows reach 2^10 or more in these units)
+// covers differences below the smallest normal number.
+__global__ void __launch_bounds__(kSubsPerBlock * kBoxDim)
+pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ perm,
+                 const int32_t* __restrict__ lab, const int32_t* __restrict__ kstart, int64_t n,
+                 int64_t subs, float eps, const Ctrl* __restrict__ ctrl,
+                 float* __restrict__ box32, int32_t* __restrict__ substart) {
+  const int t = threadIdx.x & (kBoxDim - 1);
+  const int64_t sub = (int64_t)blockIdx.x * kSubsPerBlock + (threadIdx.x / kBoxDim);
+  if (sub >= subs) return;
+  const int64_t r0 = 32 * sub;
+  const int rows = n - r0 < 32 ? (int)(n - r0) : 32;
+  float lo = INFINITY, hi = 0.0f;
+#pragma unroll 8
+  for (int i = 0; i < rows; ++i) {
+    const float v = pdist[(int64_t)perm[r0 + i] * kPivots + t];
+    lo = fminf(lo, v);
+    hi = fmaxf(hi, v);
+  }
+  const double pmax = __longlong_as_double((long long)ctrl->pmax_bits);
+  const float w = (float)(pmax * (1.0 + 0x1p-20)) + 0x1p-6f;
+  box32[sub * (2 * kBoxDim) + t] = lo * (1.0f - eps) - w;
+  box32[sub * (2 * kBoxDim) + kBoxDim + t] = hi * (1.0f + eps) + w;
+  if (t == 0) substart[sub] = kstart[lab[perm[r0]]];
+}
+
+// Boxes of the stages (nsub sub-tiles each) from those of their sub-tiles.
+__global__ void __launch_bounds__(256)
+stage_box_kernel(const float* __restrict__ box32, int64_t subs, int64_t stages, int nsub,
+                 float* __restrict__ sbox) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t st = i / (2 * kBoxDim);
+  const int t = (int)(i % (2 * kBoxDim));
+  if (st >= stages) return;
+  const int64_t s0 = st * nsub, s1 = s0 + nsub < subs ? s0 + nsub : subs;
+  float v = box32[s0 * (2 * kBoxDim) + t];
+  for (int64_t s = s0 + 1; s < s1; ++s) {
+    const float o = box32[s * (2 * kBoxDim) + t];
+    v = t < kBoxDim ? fminf(v, o) : fmaxf(v, o);
+  }
+  sbox[i] = v;
+}
+
+// Work estimate of every query tile: the stages its box cannot rule out at an
+// estimated distance of the K'-th neighbour.  Pivots: the rows of a sub-tile
+// lie within twice its smallest pivot distance of each other; a sub-tile far
+// above both its neighbours (one that holds rows of two clusters) counts as the
+// larger of them, then the largest of the tile counts.  One wave per tile; at most kPlanSamples stages are tested, evenly
+// spaced.  The estimate only balances the pieces (at 10^5 rows of 32 and 10^6
+// of 64 it is within 1% of the stages scanned).
+constexpr int kPlanSamples = 2048;
+
+__global__ void __launch_bounds__(256)
+plan_estimate_kernel(const float* __restrict__ box32, const float* __restrict__ sbox,
+                     int64_t stages, int64_t sub0, int64_t nsubs, int subs_per_tile,
+                     int64_t tiles, int prune, int32_t* __restrict__ rec) {
+  const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
+  if (t >= tiles) return;  // uniform per wave
+  const int64_t s0 = t * subs_per_tile;
+  const int64_t s1 = s0 + subs_per_tile < nsubs ? s0 + subs_per_tile : nsubs;
+  // Lane t < 32 holds entry t of the tile's box (lo, then hi).
+  const int e = lane & (2 * kBoxDim - 1);
+  float v = e < kBoxDim ? INFINITY : -INFINITY;
+  // (near: the sub-tile's smallest upper end; two sub-tiles trail.)
+  float near = 0.0f, n1 = INFINITY, n2 = INFINITY;
+  for (int64_t s = s0 - 2; s <= s1; ++s) {
+    float o = INFINITY;
+    if (s >= 0 && s < nsubs) {
+      o = box32[(sub0 + s) * (2 * kBoxDim) + e];
+      if (s >= s0 && s < s1) v = e < kBoxDim ? fminf(v, o) : fmaxf(v, o);
+    }
+    if (prune != kPrunePivot) continue;
+    o = e < kBoxDim ? INFINITY : o;
+    for (int off = 32; off > 0; off >>= 1) o = fminf(o, __shfl_xor(o, off, 64));
+    // (Off the ends of the rows the neighbour's place is empty: it counts as 0.)
+    const float a = n2 < INFINITY ? n2 : 0.0f, b = o < INFINITY ? o : 0.0f;
+    if (s > s0) near = fmaxf(near, fminf(n1, fmaxf(a, b)));
+    n2 = n1;
+    n1 = o;
+  }
+  float lo[kBoxDim], hi[kBoxDim];
+#pragma unroll
+  for (int i = 0; i < kBoxDim; ++i) {
+    lo[i] = __shfl(v, i, 64);
+    hi[i] = __shfl(v, kBoxDim + i, 64);
+  }
+  float lim;  // squared
+  if (prune == kPrunePivot) {
+    lim = 2.0f * near;
+    lim *= lim;
+  } else {
+    lim = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kBoxDim; ++i) lim += (hi[i] - lo[i]) * (hi[i] - lo[i]);
+    lim *= 0.0625f;  // a quarter of the tile's diagonal
+  }
+  const int64_t step = (stages + kPlanSamples - 1) / kPlanSamples;
+  int32_t cnt = 0, seen = 0;
+  for (int64_t s = (int64_t)lane * step; s < stages; s += 64 * step) {
+    const float4* b = reinterpret_cast<const float4*>(sbox + s * (2 * kBoxDim));
+    float lb = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kBoxDim / 4; ++i) {
+      const float4 l4 = b[i], h4 = b[kBoxDim / 4 + i];
+      const float g[4] = {fmaxf(l4.x - hi[4 * i], lo[4 * i] - h4.x),
+                          fmaxf(l4.y - hi[4 * i + 1], lo[4 * i + 1] - h4.y),
+                          fmaxf(l4.z - hi[4 * i + 2], lo[4 * i + 2] - h4.z),
+                          fmaxf(l4.w - hi[4 * i + 3], lo[4 * i + 3] - h4.w)};
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float gc = fmaxf(g[c], 0.0f);
+        lb = prune == kPrunePivot ? fmaxf(lb, gc * gc) : lb + gc * gc;
+      }
+    }
+    ++seen;
+    cnt += lb > lim ? 0 : 1;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    cnt += __shfl_xor(cnt, off, 64);
+    seen += __shfl_xor(seen, off, 64);
+  }
+  if (lane == 0) rec[3 * t + 2] = (int32_t)((int64_t)cnt * stages / (seen > 0 ? seen : 1)) + 1;
+}
+
+// Pieces per tile (one workgroup).  Tiles longer than a target length are cut
+// into equal pieces.  The target is picked from a geometric series by the time
+// it should take: the work over the slots (and half a mean piece idle at the
+// end), and no less than the longest piece, plus a charge for the number of
+// pieces.  A scan of L stages
+// costs L for the distances and kSelCost L for the selection while nearly every
+// sub-tile holds a survivor, i.e. up to l0 stages (1024 K' rows: 32 x 32 pairs
+// a sub-tile, each in the first K' of t rows with probability K'/t); beyond,
+// the selection grows with the logarithm only, so cutting such a scan repeats
+// it.  Each piece costs `fixed` on top (its first rows fill the lists: 60 us at
+// K' = 32).  At 10^5 rows of 32 (Gaussian mixture, 2% outliers, K' = 32) the outliers'
+// tiles scan everything: cut, the tile kernel takes 1.2 ms instead of 1.64.  At
+// 10^6 rows of 64 cutting tiles of 800 stages (l0 = 256) in two took 59 ms
+// instead of 47.  Where the last round would leave compute units idle, its
+// tiles (those taken last: the first ones) are cut too, as tail_pieces does.
+constexpr int kPlanThreads = 1024;
+constexpr int kMaxPieces = 32;
+constexpr float kPruneWorth = 0.8f;
+constexpr float kSelCost = 1.7f;
+constexpr float kPieceCharge = 0.25f;
+
+__global__ void __launch_bounds__(kPlanThreads)
+plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, float l0, float fixed,
+                   int32_t* __restrict__ plan, int64_t rec_at) {
+  __shared__ float red[3][kPlanThreads / 64];
+  __shared__ int32_t wsum[kPlanThreads / 64];
+  int32_t* rec = plan + rec_at;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // Sums of v and w and maximum of m over the workgroup.
+  auto block_red = [&](float& v, float& w, float& m) {
+    for (int off = 32; off > 0; off >>= 1) {
+      v += __shfl_xor(v, off, 64);
+      w += __shfl_xor(w, off, 64);
+      m = fmaxf(m, __shfl_xor(m, off, 64));
+    }
+    __syncthreads();
+    if (lane == 0) {
+      red[0][wave] = v;
+      red[1][wave] = w;
+      red[2][wave] = m;
+    }
+    __syncthreads();
+    v = w = m = 0.0f;
+    for (int i = 0; i < kPlanThreads / 64; ++i) {
+      v += red[0][i];
+      w += red[1][i];
+      m = fmaxf(m, red[2][i]);
+    }
+  };
+  float total = 0.0f, top = 0.0f, unused = 0.0f;
+  for (int64_t t = tid; t < tiles; t += kPlanThreads) {
+    const float e = (float)rec[3 * t + 2];
+    total += e;
+    top = fmaxf(top, e);
+  }
+  block_red(total, unused, top);
+  // Where the boxes rule out less than a fifth of the pairs the plain scan is
+  // the faster one (its sequence of stages is known): 6.1 ms against 6.6 at
+  // 97,549 uniform rows of 26 (K' = 64), 27.1 against 29.4 at 269,454 of 65.
+  if (total > kPruneWorth * (float)tiles * (float)stages) {
+    if (tid == 0) plan[0] = -1;
+    return;  // uniform over the workgroup
+  }
+  auto pieces_of = [&](float est, float target) -> float {
+    const float p = ceilf(est / target - 1e-4f);
+    return p < 1.0f ? 1.0f : p < kMaxPieces ? p : (float)kMaxPieces;
+  };
+  auto cost = [&](float l) -> float {
+    return fixed + l + kSelCost * (l < l0 ? l : l0 * (1.0f + __logf(l / l0)));
+  };
+  // (All of this is uniform over the workgroup.)
+  float best = INFINITY, target = top, count = (float)tiles;
+  const float low = fmaxf(4.0f, total / slots * 0.25f);
+  for (float c = top; c >= low || c == top; c *= 0.62f) {
+    float n = 0.0f, work = 0.0f, len = 0.0f;
+    for (int64_t t = tid; t < tiles; t += kPlanThreads) {
+      const float est = (float)rec[3 * t + 2], p = pieces_of(est, c), one = cost(est / p);
+      n += p;
+      work += p * one;
+      len = fmaxf(len, one);
+    }
+    block_red(n, work, len);
+    if (n - (float)tiles > (float)cap) break;  // shorter targets need more
+    // (More pieces than slots: half a piece of idle time at the end.)
+    const float span = fmaxf(n > slots ? work / slots + 0.5f * work / n : 0.0f, len) *
+                       (1.0f + kPieceCharge * (1.0f - (float)tiles / n));
+    if (span < best) {
+      best = span;
+      target = c;
+      count = n;
+    }
+  }
+  // The last round's tiles.
+  const int64_t tw = (int64_t)count % slots;
+  int tailp = 1;
+  if (tw > 0 && tw < cus && tw < tiles) {
+    float tbest = 1.0f;
+    for (int p = 2; p <= 8; ++p) {
+      if (count - (float)tiles + (float)(tw * (p - 1)) > (float)cap) break;
+      const float c = (float)((tw * p + slots - 1) / slots) / p + 0.02f * (p - 1);
+      if (c < tbest - 1e-6f) {
+        tbest = c;
+        tailp = p;
+      }
+    }
+  }
+  auto pieces = [&](int64_t t) -> int32_t {
+    const int32_t p = (int32_t)pieces_of((float)rec[3 * t + 2], target);
+    return t < tw && p < tailp && rec[3 * t + 2] >= 4 * tailp ? tailp : p;
+  };
+  int32_t base = 0;
+  for (int64_t t0 = 0; t0 < tiles; t0 += kPlanThreads) {
+    const int64_t t = t0 + tid;
+    const int32_t ex = t < tiles ? pieces(t) - 1 : 0;
+    const int32_t incl = wave_incl_sum(ex, lane);
+    __syncthreads();
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int32_t at = base + incl - ex;
+    int32_t all = 0;
+    for (int w = 0; w < kPlanThreads / 64; ++w) {
+      at += w < wave ? wsum[w] : 0;
+      all += wsum[w];
+    }
+    if (t < tiles) {
+      rec[3 * t] = at;
+      rec[3 * t + 1] = ex;
+      for (int32_t i = 0; i < ex; ++i) {
+        plan[1 + 2 * (int64_t)(at + i)] = (int32_t)t;
+        plan[2 + 2 * (int64_t)(at + i)] = i + 1;
+      }
+    }
+    base += all;
+  }
+  if (tid == 0) plan[0] = base;
 }
 
 }  // namespace
@@ -224,6 +658,21 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
                                  : assign_small_kernel<16>;
     hipLaunchKernelGGL(kern, dim3(ga), dim3(kAssignThreads), 0, st, a.xr, n, (int)p.d, G,
                        reinterpret_cast<const float4*>(a.oseed), a.lab);
+  } else if (p.prune == kPrunePivot) {
+    if (G != kPivots * kRadBins) return hipErrorInvalidValue;
+    int32_t* const srow = reinterpret_cast<int32_t*>(a.oseed);
+    const int m = seed_samples(n, (int)p.d);
+    int tps = 2;  // threads per sample
+    while (m * tps * 2 <= kSeedThreads && tps < 64) tps *= 2;
+    const size_t lds = sizeof(float) * (size_t)m * (size_t)(p.d + 1);
+    hipError_t e = hipFuncSetAttribute((const void*)pivot_seed_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
+                       m, tps, a.ctrl, p.scale_exp, srow);
+    hipLaunchKernelGGL(assign_pivot_kernel, dim3(ga), dim3(kAssignThreads),
+                       sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.ctrl,
+                       p.scale_exp, srow, a.pdist, a.lab);
   } else {
     if (G != kWideGroups) return hipErrorInvalidValue;
     hipLaunchKernelGGL(assign_kernel, dim3(ga), dim3(kAssignThreads),
@@ -232,9 +681,40 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
   hipLaunchKernelGGL(count_kernel, dim3((unsigned)nb), dim3(256), 0, st, a.lab, n, G, a.bcnt);
   hipLaunchKernelGGL(block_offsets_kernel, dim3((unsigned)((G + 3) / 4)), dim3(256), 0, st,
                      a.bcnt, nb, G, a.boff, a.cstart);
-  hipLaunchKernelGGL(group_starts_kernel, dim3(1), dim3(64), 0, st, G, a.cstart);
-  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nb), dim3(64), 0, st, a.lab, n, G, a.boff,
-                     a.cstart, a.perm);
+  if (p.prune == kPrunePivot)
+    hipLaunchKernelGGL(pivot_starts_kernel, dim3(1), dim3(kPivots * kRadBins), 0, st, a.cstart,
+                       a.kstart);
+  else
+    hipLaunchKernelGGL(group_starts_kernel, dim3(1), dim3(64), 0, st, G, a.cstart);
+  int bits = 0;
+  while ((1 << bits) < G) ++bits;
+  hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nb), dim3(64), 0, st, a.lab, n, G, bits,
+                     a.boff, a.cstart, a.perm);
+  return hipGetLastError();
+}
+
+hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t st) {
+  const int64_t subs = p.nr_pad / 32;
+  const int64_t stages = (p.nr + p.stage_rows - 1) / p.stage_rows;
+  const float eps = (float)(p.d + 16) * 0x1p-24f;
+  hipLaunchKernelGGL(pivot_box_kernel, dim3((unsigned)((subs + kSubsPerBlock - 1) / kSubsPerBlock)),
+                     dim3(kSubsPerBlock * kBoxDim), 0, st, a.pdist, a.perm, a.lab, a.kstart, p.nr,
+                     subs, eps, a.ctrl, a.box32, a.substart);
+  hipLaunchKernelGGL(stage_box_kernel, dim3((unsigned)((stages * 2 * kBoxDim + 255) / 256)),
+                     dim3(256), 0, st, a.box32, subs, stages, p.stage_rows / 32, a.sbox);
+  return hipGetLastError();
+}
+
+hipError_t launch_plan(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows, int slots,
+                       int cus, hipStream_t st) {
+  const int64_t tiles = (q_rows + p.tile_rows - 1) / p.tile_rows;
+  const int64_t stages = (p.nr + p.stage_rows - 1) / p.stage_rows;
+  hipLaunchKernelGGL(plan_estimate_kernel, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
+                     a.box32, a.sbox, stages, q_begin / 32, (q_rows + 31) / 32, p.tile_rows / 32,
+                     tiles, p.prune, a.plan + a.plan_tiles);
+  hipLaunchKernelGGL(plan_pieces_kernel, dim3(1), dim3(kPlanThreads), 0, st, tiles, stages, slots,
+                     cus, (int)a.plan_cap, 1024.0f * p.kprime / p.stage_rows,
+                     200.0f * p.kprime / p.stage_rows, a.plan, a.plan_tiles);
   return hipGetLastError();
 }
 

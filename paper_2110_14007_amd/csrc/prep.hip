@@ -459,10 +459,12 @@ hipError_t launch_prep(const Plan& p, const Args& a, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   switch (p.precision) {
-    case TOD_PREC_FP32: return launch_quantise<float>(p, a, st);
-    case TOD_PREC_FP16: return launch_quantise<_Float16>(p, a, st);
-    default: return launch_quantise<__bf16>(p, a, st);
+    case TOD_PREC_FP32: e = launch_quantise<float>(p, a, st); break;
+    case TOD_PREC_FP16: e = launch_quantise<_Float16>(p, a, st); break;
+    default: e = launch_quantise<__bf16>(p, a, st); break;
   }
+  if (e != hipSuccess || !p.prune) return e;
+  return launch_boxes(p, a, st);
 }
 
 }  // namespace tod

@@ -92,7 +92,7 @@ range_tile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   constexpr int W = 4, NT = 256;
   constexpr int KC = LY::k16;
   constexpr int ROWB = LY::rowb;
-  constexpr int NS = LY::ns;
+  constexpr int NS = mt::stage_subs_base(DPAD);
   constexpr int TR = 32 * NS;  // reference rows per stage
   constexpr int STAGE = TR * ROWB;
   constexpr int CPR = LY::cpr;
@@ -277,7 +277,7 @@ template <typename ET, int DPAD>
 hipError_t launch_range(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows, bool fill,
                         hipStream_t st) {
   using LY = mt::Layout<DPAD, false>;
-  const size_t lds = (size_t)2 * 32 * LY::ns * LY::rowb + (size_t)2 * 32 * LY::ns * sizeof(float);
+  const size_t lds = (size_t)2 * 32 * mt::stage_subs_base(DPAD) * LY::rowb + (size_t)2 * 32 * mt::stage_subs_base(DPAD) * sizeof(float);
   const auto kern = fill ? range_tile_kernel<ET, DPAD, true> : range_tile_kernel<ET, DPAD, false>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)kern,

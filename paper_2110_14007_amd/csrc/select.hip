@@ -226,11 +226,7 @@ recheck_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     const int64_t qi = a.perm ? (int64_t)a.perm[qpos] : qpos;
     const double ni = a.n64_q[qpos], rho_i = a.rho_q[qpos];
     // Final aggregation of the per-split candidate lists (Section 6.1).
-    // Rows of the tail split have one list per scanned piece.
-    const bool tl = ql >= a.tail_q0;
-    const int nlists = tl ? a.tail_parts : a.splits;
-    const uint64_t* src =
-        tl ? a.ptail + (ql - a.tail_q0) * a.tail_parts * KP : a.partial + ql * a.splits * KP;
+    const RowLists rl = row_lists<KP>(a, ql);
     // With runs (a.runs == 2, K' = 128) a list holds two ascending runs of
     // 64, each the best of one piece of the scan order: they are merged into
     // one ascending list, and `cap`, the smaller of the run ends, bounds every
@@ -249,15 +245,16 @@ recheck_kernel(Args a, int64_t q_begin, int64_t q_rows) {
 #pragma unroll
     for (int r = 0; r < EL; ++r) {
       const int e = r * 64 + lane;
-      list[r] = e < KP ? src[e] : kEmpty;
+      list[r] = e < KP ? rl.first[e] : kEmpty;
     }
     sort_runs(list);
-    for (int s = 1; s < nlists; ++s) {
+    for (int s = 1; s < rl.n; ++s) {
+      const uint64_t* src = rl.rest + (int64_t)(s - 1) * rl.stride;
       uint64_t other[EL];
 #pragma unroll
       for (int r = 0; r < EL; ++r) {
         const int e = r * 64 + lane;
-        other[r] = e < KP ? src[(int64_t)s * KP + e] : kEmpty;
+        other[r] = e < KP ? src[e] : kEmpty;
       }
       sort_runs(other);
       merge_lists<EL>(list, other, lane);
@@ -377,12 +374,6 @@ recheck_lanes_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // A group past the block's rows repeats the wave's first query and writes
   // nothing.
   auto row_of = [&](int64_t qb) { return qb + grp < q_rows ? qb + grp : qb; };
-  // Lists of the row's splits (or of the pieces of a tail-split row).
-  auto lists_of = [&](int64_t ql, int& nlists) -> const uint64_t* {
-    const bool tl = ql >= a.tail_q0;
-    nlists = tl ? a.tail_parts : a.splits;
-    return tl ? a.ptail + (ql - a.tail_q0) * a.tail_parts * KP : a.partial + ql * a.splits * KP;
-  };
   // A trip's first loads (its list entry, input row, squared norm and radius)
   // are issued one trip ahead; its outputs are written one trip late, after
   // the next trip's loads.  Stores count against the same in-order wait
@@ -394,9 +385,8 @@ recheck_lanes_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   };
   auto fetch = [&](int64_t qb) __attribute__((always_inline)) {
     const int64_t ql = row_of(qb), qpos = q_begin + ql;
-    int nl;
     Ahead x;
-    x.v = lists_of(ql, nl)[g];
+    x.v = row_lists<KP>(a, ql).first[g];
     x.qi = a.perm ? (int64_t)a.perm[qpos] : qpos;
     x.ni = a.n64_q[qpos];
     x.rho = a.rho_q[qpos];
@@ -430,14 +420,13 @@ recheck_lanes_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     // the elementwise minimum holds the K' smallest of both as a bitonic
     // sequence, which a bitonic merge sorts.  Groups with fewer lists than
     // the wave's most merge empty ones.
-    int nlists;
-    const uint64_t* src = lists_of(row_of(qb), nlists);
+    const RowLists rl = row_lists<KP>(a, row_of(qb));
     uint64_t v = cur.v;
-    int nlw = nlists;
+    int nlw = rl.n;
 #pragma unroll
     for (int off = KP; off < 64; off <<= 1) nlw = max(nlw, __shfl_xor(nlw, off, 64));
     for (int s = 1; s < nlw; ++s) {
-      v = umin64(v, s < nlists ? src[(int64_t)s * KP + (KP - 1 - g)] : kEmpty);
+      v = umin64(v, s < rl.n ? rl.rest[(int64_t)(s - 1) * rl.stride + (KP - 1 - g)] : kEmpty);
 #pragma unroll
       for (int st = KP / 2; st > 0; st >>= 1) {
         const uint64_t o = lane_xor64(v, st);

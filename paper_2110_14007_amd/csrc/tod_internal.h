@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "../../include/tod.h"
+#include "mtile_shape.h"
 
 namespace tod {
 
@@ -42,7 +43,11 @@ struct Plan {
   int32_t lists;       // int32 / fp64 neighbour lists kept in the workspace (LOF, score
                        // aggregates, classifier)
   int32_t order;       // 1: grouped scan order (order.hip), X against X only
-  int32_t groups;      // seed groups of the grouped order (order_groups)
+  int32_t groups;      // counting-sort keys of the grouped order (order_groups)
+  int32_t prune = 0;   // kPruneNone, or the kind of the boxes the register-list tile skips
+                       // reference stages by (grouped order only)
+  int32_t stage_rows = 0;  // rows of a stage box: the tile's stage (mtile_stage_rows)
+  int32_t tile_rows = 0;   // query rows of a tile workgroup (mtile_tile_rows)
   int32_t runs = 1;    // 2: the register-list tile scans the references in 2 S pieces of the
                        // scan order with lists of K' / 2; each query's K' slots per split
                        // then hold two ascending runs (rows of 256+ elements, K' = 128)
@@ -88,7 +93,7 @@ inline int tail_pieces(int64_t tw, int64_t slots, int64_t cus, int pmax, bool au
 struct Layout {
   size_t ctrl, mu64, mu32, colpart, xq_r, xq_q, hn_r, n64_q, rho_q, partial, ptail, worklist,
       fbtau, fbpart, fbidx, idx32, d64, lrd, kdist, perm, lab, oseed, cstart, bcnt, boff,
-      total;
+      kstart, box32, sbox, substart, plan, total;
   int32_t colpart_blocks;
 };
 
@@ -166,6 +171,19 @@ struct Args {
   int32_t* cstart;     // first position of each group [groups + 1]
   int32_t* bcnt;       // rows per group in each block of kOrdRows rows
   int32_t* boff;       // first position of each block's rows of each group
+  // Pruned scan (all null / 0 without it; see order.hip).
+  int32_t prune;       // kPruneNone, kPrunePivot or kPruneBox
+  int32_t stage_rows;  // rows of a stage box
+  int32_t tile_rows;   // query rows of a tile workgroup
+  int32_t* kstart;     // per key: first position of its group's class
+  float* pdist;        // distances of the input rows to the kPivots seeds [nr x kPivots]
+                       // (lies over the partial lists: dead once the boxes are made)
+  float* box32;        // boxes of the 32-row sub-tiles [nr_pad / 32][2 kBoxDim]: lo, hi
+  float* sbox;         // boxes of the stages [ceil(nr / stage_rows)][2 kBoxDim]
+  int32_t* substart;   // per sub-tile: position where its scan starts after the home stages
+  int32_t* plan;       // work plan of a launch (plan_words): extra pieces and the tiles' pieces
+  int64_t plan_tiles;  // first word of the plan's per-tile records
+  int64_t plan_cap;    // extra pieces the tail region holds
   int32_t* idx32;      // [nq x k] neighbour ids (LOF)
   double* d64;         // [nq x k] exact distances (LOF)
   double* lrd;         // [nq] LOF scratch
@@ -218,6 +236,59 @@ __host__ __device__ constexpr double fold_const(int precision) {
 constexpr int kOrdMaxC = 1024;
 constexpr int kOrdRows = 1024;
 constexpr int64_t kOrderMinRows = 4096;
+// Pruned scan.  A box holds, per dimension of a kBoxDim-dimensional space, the
+// smallest and the largest value over a set of rows.  kPrunePivot: the
+// dimensions are the distances to kPivots seed rows (each 1-Lipschitz, so a
+// gap between two boxes in any dimension bounds the rows' distances from
+// below).  kPruneBox: the quantised columns themselves (at most kBoxDim; the
+// gaps add up in squares).
+constexpr int kPruneNone = 0, kPrunePivot = 1, kPruneBox = 2;
+constexpr int kBoxDim = 16;
+constexpr int kPivots = 16;
+constexpr int kRadBins = 64;  // distance bins per seed group (two per octave of D^2)
+// Words of the work plan: [0] extra pieces (-1: the boxes rule out too little,
+// the plain scan runs instead), [1 + 2 e] tile and [2 + 2 e] piece
+// of extra piece e, then per tile its first extra piece, its extra pieces and
+// its estimated stages.
+inline int64_t plan_words(int64_t tiles, int64_t extra) { return 1 + 2 * extra + 3 * tiles; }
+// Extra pieces the tail region has room for.
+inline int64_t plan_extra(const Plan& p) {
+  return p.tile_rows > 0 ? p.tail_lists / p.tile_rows : 0;
+}
+// Boxes of the sub-tiles and stages in the grouped order (after quantisation).
+hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t s);
+// Work plan of the tile launch over query rows [q_begin, q_begin + q_rows)
+// on a GPU of `cus` compute units that runs `slots` of its workgroups at once.
+hipError_t launch_plan(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows, int slots,
+                       int cus, hipStream_t s);
+// The partial lists of query row ql of a block: list 0 at first, list s >= 1
+// at rest + (s - 1) * stride.
+struct RowLists {
+  const uint64_t* first;
+  const uint64_t* rest;
+  int64_t stride;
+  int n;
+};
+template <int KP>
+__device__ __forceinline__ RowLists row_lists(const Args& a, int64_t ql) {
+  RowLists r;
+  if (a.plan && a.plan[0] >= 0) {  // one list per piece of the row's tile (the work plan)
+    const int64_t t = ql / a.tile_rows;
+    const int32_t* pt = a.plan + a.plan_tiles + 3 * t;
+    r.n = 1 + pt[1];
+    r.first = a.partial + ql * KP;
+    r.stride = (int64_t)a.tile_rows * KP;
+    r.rest = a.ptail + ((int64_t)pt[0] * a.tile_rows + (ql - t * a.tile_rows)) * KP;
+    return r;
+  }
+  // Rows of the tail split have one list per scanned piece.
+  const bool tl = ql >= a.tail_q0;
+  r.n = tl ? a.tail_parts : a.splits;
+  r.first = tl ? a.ptail + (ql - a.tail_q0) * a.tail_parts * KP : a.partial + ql * a.splits * KP;
+  r.rest = r.first + KP;
+  r.stride = KP;
+  return r;
+}
 int32_t order_groups(int64_t nr, int64_t d);
 int32_t order_blocks(int64_t nr);
 hipError_t launch_order(const Plan& p, const Args& a, hipStream_t s);

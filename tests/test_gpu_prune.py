@@ -1,0 +1,77 @@
+"""GPU parity of the pruned scan: stages whose box lies farther from a wave's
+queries than their K'-th neighbours are skipped.  Every output must equal the
+plain order's (reorder = -1) bit for bit, and sampled rows the oracle's.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from tests.compare import compare_knn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible MI355X"
+    from paper_2110_14007_amd import tod
+    from oracle import oracle
+    return torch, tod, oracle
+
+
+def data(kind, n, d, rng):
+    if kind == "clusters":  # ten clusters and outliers: most stages are ruled out
+        c = 5.0 * rng.standard_normal((10, d))
+        x = c[rng.integers(0, 10, n)] + rng.standard_normal((n, d))
+        x[: n // 100] = 10.0 * rng.standard_normal((n // 100, d))
+        rng.shuffle(x)
+    elif kind == "uniform":  # nothing is ruled out: the plain scan takes over
+        x = rng.random((n, d))
+    elif kind == "shells":  # one cluster, rows far from every pivot, duplicates
+        x = rng.standard_normal((n, d)) * np.where(rng.random((n, 1)) < 0.1, 8.0, 1.0)
+        x[n // 2: n // 2 + 300] = x[:300]
+    else:  # two values in all
+        x = np.where(rng.random((n, 1)) < 0.5, 1.0, -1.0) * np.ones((1, d))
+        x[:, 0] += 1e-3 * rng.standard_normal(n)
+    return x.astype(np.float32)
+
+
+# Sizes around the tile's edges: rows of 17 to 512 elements (stages of one to
+# eight sub-tiles, boxes of one to four stages), ragged counts, K' = 16 to 128
+# (two runs), query blocks, more tiles than the GPU runs at once with a part
+# round at the end (66,001 rows of 20: the tail split under the plain scan).
+@pytest.mark.parametrize("kind,n,d,k,opt", [
+    ("clusters", 20011, 17, 5, {}),
+    ("clusters", 17001, 33, 20, {}),
+    ("clusters", 30000, 64, 10, {"query_block": 8192}),
+    ("clusters", 16385, 100, 30, {"precision": "bf16"}),
+    ("clusters", 20000, 200, 50, {"precision": "bf16"}),
+    ("clusters", 17000, 300, 12, {}),
+    ("clusters", 16400, 512, 50, {"precision": "bf16"}),
+    ("clusters", 5000, 40, 9, {"reorder": 1, "ref_splits": 1, "tail_parts": 3}),
+    ("uniform", 66001, 20, 10, {}),
+    ("uniform", 33333, 70, 20, {}),
+    ("shells", 24007, 24, 15, {}),
+    ("two", 16999, 30, 7, {}),
+])
+def test_pruned_equals_plain(env, kind, n, d, k, opt):
+    torch, tod, oracle = env
+    rng = np.random.default_rng(n + d)
+    x = data(kind, n, d, rng)
+    print("pruned", kind, n, d, k, opt, flush=True)
+    sys.stdout.flush()
+    xd = torch.from_numpy(x).cuda()
+    st = tod.new_stats()
+    opt = dict(opt, reorder=1)
+    got = tod.tod_knn_score(xd, k, tod.options(**opt), stats=st, return_lists=True)
+    assert st.reordered
+    plain = dict(opt, reorder=-1)
+    plain.pop("tail_parts", None)
+    ref = tod.tod_knn_score(xd, k, tod.options(**plain), return_lists=True)
+    for u, v in zip(got, ref):
+        assert torch.equal(u, v)
+    rows = np.sort(rng.choice(n, 64, replace=False))
+    oidx, odist = oracle.knn_self(x, k, rows=rows)
+    compare_knn(x, x, rows, got[1].cpu().numpy()[rows], got[2].cpu().numpy()[rows], oidx, odist)
