@@ -115,7 +115,9 @@ void set_splits(Plan* p, int64_t s) {
 // The pruned scan's kind and the grouped order's keys, which follow from it.
 static void set_prune(Plan* p, int32_t kind) {
   p->prune = kind;
-  p->groups = kind == kPrunePivot ? kPivots * kRadBins : order_groups(p->nr, p->d);
+  p->groups = kind == kPrunePivot ? kPivots * kRadBins
+              : kind == kPruneBox ? kd_leaves(p->nr)
+                                  : order_groups(p->nr, p->d);
 }
 
 tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, int32_t self,
@@ -179,7 +181,7 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   // (The pruned scan of X against X cuts its own work: one split.)
   const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
                       prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
-                      (nr >= kPruneMinRows || o.reorder > 0) && d > kBoxDim;
+                      (nr >= kPruneMinRows || o.reorder > 0);
   set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr));
   p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
@@ -231,14 +233,14 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   if (p->tile_kind == 1) {
     const int32_t r = (int32_t)kp / p->runs / 2;
     // (A box holds at least kUnitRows rows.)
-    p->stage_rows = 32 * mt::stage_subs(p->dpad_t, p->fold, r);
+    p->stage_rows = 32 * mt::stage_subs(p->dpad_t, p->fold, r, true);
     if (p->stage_rows < mt::kUnitRows) p->stage_rows = mt::kUnitRows;
-    p->tile_rows = 32 * mt::tile_waves(p->dpad_t, p->fold, r) *
+    p->tile_rows = 32 * mt::tile_waves(p->dpad_t, p->fold, r, true) *
                    mt::query_groups(p->dpad_t, p->fold, r);
   }
   // Pruned scan: wherever the grouped order applies (its boxes cost 4 bytes
   // a row and a stage test per 64 stages).
-  set_prune(p, p->order && d > kBoxDim ? kPrunePivot : kPruneNone);
+  set_prune(p, !p->order ? kPruneNone : d > kBoxDim ? kPrunePivot : kPruneBox);
   // Tail split of the register-list tile with one reference split (not with
   // runs: their pieces already halve every workgroup's scan).
   p->tail_parts = 1;
@@ -296,7 +298,7 @@ Layout make_layout(const Plan& p) {
   } else {
     L.perm = L.lab = L.oseed = L.cstart = L.bcnt = L.boff = 0;
   }
-  L.kstart = L.box32 = L.sbox = L.substart = L.plan = 0;
+  L.kstart = L.box32 = L.sbox = L.xbox = L.substart = L.plan = 0;
   if (p.prune) {
     const size_t subs = (size_t)(p.nr_pad / 32);
     const size_t stages = (size_t)((p.nr + p.stage_rows - 1) / p.stage_rows);
@@ -304,6 +306,7 @@ Layout make_layout(const Plan& p) {
     L.kstart = take(sizeof(int32_t) * (size_t)p.groups);
     L.box32 = take(sizeof(float) * 2 * kBoxDim * subs);
     L.sbox = take(sizeof(float) * 2 * kBoxDim * stages);
+    L.xbox = take(sizeof(float) * 2 * kBoxDim * ((stages + 63) / 64));
     L.substart = take(sizeof(int32_t) * subs);
     L.plan = take(sizeof(int32_t) * (size_t)plan_words((int64_t)tiles, kTailLists / p.tile_rows));
   }
@@ -361,11 +364,11 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   const size_t per = (size_t)q.kprime * sizeof(uint64_t);  // partial-list bytes per row and split
   const bool want = o.reorder > 0 || (o.reorder == 0 && q.nr >= kOrderMinRows);
   const bool may_order = q.self && q.tile_kind == 1 && want;
-  const int32_t prune = q.d > kBoxDim ? kPrunePivot : kPruneNone;
+  const int32_t prune = q.d > kBoxDim ? kPrunePivot : kPruneBox;
   size_t need = 0;
   // (2: the order and the pruned scan, only while the block keeps
   // kPruneMinBlock rows; 1: the order alone; 0: neither.)
-  for (int with_order = may_order ? (prune ? 2 : 1) : 0; with_order >= 0; --with_order) {
+  for (int with_order = may_order ? 2 : 0; with_order >= 0; --with_order) {
     Plan f = q;
     f.query_block = 0;  // no partial lists: the fixed part of the layout
     f.order = with_order ? 1 : 0;
@@ -603,6 +606,7 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
     a.pdist = (float*)(base + L.partial);
     a.box32 = (float*)(base + L.box32);
     a.sbox = (float*)(base + L.sbox);
+    a.xbox = (float*)(base + L.xbox);
     a.substart = (int32_t*)(base + L.substart);
     // The work plan: one run, one split, pieces chosen by the planner.
     if (p.runs == 1 && p.splits == 1 && p.tail_auto && tod::plan_extra(p) > 0) {

@@ -327,11 +327,11 @@ constexpr int queue_slots() { return NQ == 1 ? queue_cap<R>() : 16; }
 
 // Stage buffers, their seeds, the queues and the pruned scan's stage masks.
 __host__ __device__ constexpr size_t lds_bytes(int dpad, bool fold, int w, int ns, int qcap,
-                                               int nq) {
+                                               int nq, bool pr) {
   return (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * (dpad == 16 ? 32 : dpad * 2 + 16) +
          (fold ? 0 : (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * sizeof(uint2)) +
          (size_t)w * nq * qcap * 64 * sizeof(uint2) +
-         (dpad == 16 ? 0 : (size_t)2 * w * sizeof(uint64_t));
+         (pr ? (size_t)2 * w * sizeof(uint64_t) : 0);
 }
 
 // At least two waves per SIMD for lists of up to 32 entries and rows of up to
@@ -854,15 +854,16 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // and so the stream they read.  Otherwise the split is scanned in order.
   // With the pruned scan the stages around the workgroup's own rows come
   // first (they give every query a threshold near its final one); the rest
-  // follow from the start of the rows' group on, wrapping round.  A cut scan's
-  // piece takes every parts-th unit of that order (without the boxes,
-  // contiguous pieces of it).  The pruned scan's unit is the box: a stage, or
+  // follow from the start of the rows' group on (rows of at most 16 elements:
+  // from their own place on), wrapping round.  A cut scan's piece takes every
+  // parts-th unit (without the boxes, a contiguous part of the order).  The pruned scan's unit is the box: a stage, or
   // as many as make up 128 rows.
   constexpr int UR = PR && TR < kUnitRows ? kUnitRows : TR;  // rows of a unit
   const int nst = (int)((r_end - r_begin + UR - 1) / UR);
   const int64_t p0 = q_begin + (int64_t)tile * (W * 32 * NQ);  // the tile's first query
   int st0 = 0, hs = 0, hn = 0;  // first stage of the rest; home stages [hs, hs + hn)
-  int nscan = nst, stepi = 1, offi = 0;
+  [[maybe_unused]] int nscan = nst, offi = 0;
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
   if constexpr (PR) {
     const int own = (int)(p0 / UR);
     constexpr int kHome = kHomeRows / UR;
@@ -871,10 +872,9 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     hs = own - hn / 2;
     hs = hs < 0 ? 0 : (hs + hn <= nst ? hs : nst - hn);
     st0 = a.substart[p0 >> 5] / UR;
-    if (st0 >= hs && st0 < hs + hn) st0 = hs + hn < nst ? hs + hn : 0;
-    stepi = parts;
     offi = pieces ? piece : 0;
-    nscan = (nst - offi + stepi - 1) / stepi;
+    st0 = uniform(st0);
+    hs = uniform(hs);
   } else {
     if (a.cstart) {
       // The last group starting at or before p0 (starts ascend; an empty group
@@ -910,39 +910,84 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     return r_begin + (int64_t)s * TR;
   };
 
-  // Pruned scan: unit of the i-th scan position.
-  [[maybe_unused]] auto unit_at = [&](int i) -> int {
-    i = i * stepi + offi;
-    if (i < hn) return hs + i;
-    i -= hn;
-    // The home units lie `skip` units past st0 in wrapping order: left out.
-    int skip = hs - st0;
-    skip = skip < 0 ? skip + nst : skip;
-    i += i >= skip ? hn : 0;
-    int s = st0 + i;
-    return s >= nst ? s - nst : s;
-  };
   // The pruned scan as a sequence of stages: next() gives the next stage's
   // first row, or -1 at the end, and `need`, whether this wave's queries need
-  // it.  64 scan positions at a time, lane l bounds the distance between the
-  // wave's query box and the box of the unit at position l from below; a unit
-  // survives if the bound does not exceed the distance its K'-th entry implies
-  // for some query of the wave.  Exactness: a skipped row's quantised squared
-  // distance D is then at least N_i + key of the query's K'-th entry, so its
-  // exact key D - N_i is no smaller than the final list's last key, which is
-  // what the certificate asks of every row left out.  The margin 2^-16 covers
-  // the rounding of the bound (at most 16 fp32 terms; the boxes are widened
-  // where they are rounded).  The workgroup stages what any wave needs.
+  // it.  After the home units come chunks of 64 consecutive units, in wrapping
+  // order from the one of st0 on.  Lane l bounds the distance between the wave's
+  // query box and the box of a chunk (64 chunks at a time) or of the chunk's unit
+  // l from below; what no wave needs is left out, the rest is staged for the
+  // workgroup.  A box is needed if the bound does not exceed the distance the
+  // K'-th entry implies for some query of the wave.  Exactness: a skipped row's
+  // quantised squared distance D is then at least N_i + key of the query's K'-th
+  // entry, so its exact key D - N_i is no smaller than the final list's last
+  // key, which is what the certificate asks of every row left out.  The margins
+  // cover the rounding: 2^-16 of the bound's (at most 16 fp32 terms; the boxes
+  // are widened where they are rounded), 2^-21 N_i of the limit's.
   // (Scalar values throughout: in vector registers the stage addresses and the
   // per-stage tests cost rows of 65 to 128 elements a fifth of their time.)
-  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-  st0 = uniform(st0);
-  hs = uniform(hs);
-  uint64_t um = 0, om = 0;  // units of the chunk: any wave's, this wave's
-  int cb = 0, cn = 0, par = 0;
+  [[maybe_unused]] uint64_t um = 0, om = 0, sm = 0;  // units: any wave's, this wave's; chunks
+  [[maybe_unused]] int sg = -1, ubase = 0, par = 0;
   [[maybe_unused]] int64_t ucur = -1, uend = 0;
   [[maybe_unused]] bool uneed = false;
-  uint64_t* const wneed = (uint64_t*)(qbase + W * NQ * kQCap * 64);  // [2][W]
+  [[maybe_unused]] const int nch = (nst + 63) >> 6, ch0 = st0 >> 6;
+  [[maybe_unused]] uint64_t* const wneed = (uint64_t*)(qbase + W * NQ * kQCap * 64);  // [2][W]
+  [[maybe_unused]] float nup[NQ];  // N_i and the limit's margin
+  if constexpr (PR) {
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+      const bool live = active && group * 32 * NQ + 32 * u + col < q_rows;
+      // (An idle column admits nothing: its limit is -inf.)
+      nup[u] = live ? (float)a.n64_q[q0 + 32 * u + col] * (1.0f + 0x1p-21f) : -INFINITY;
+    }
+  }
+  // Largest squared distance any of the wave's lists still admits.
+  [[maybe_unused]] auto limit = [&]() __attribute__((always_inline)) {
+    float lim = 0.0f;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u)
+      if (nup[u] > -INFINITY) lim = fmaxf(lim, fmaf(-2.0f, thr[u], nup[u]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lim = fmaxf(lim, __shfl_xor(lim, off, 64));
+    return lim * (1.0f + 0x1p-16f);
+  };
+  // Whether the wave needs a box (a lane's own).
+  [[maybe_unused]] auto needs = [&](const float* box, float lim) __attribute__((always_inline)) {
+    const float4* bx = reinterpret_cast<const float4*>(box);
+    bool ok = false;
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) {
+      if (group * 32 * NQ + 32 * u >= q_rows) continue;
+      // (Uniform address: the query box comes through the scalar cache.)
+      const float* qb = a.box32 +
+                        (int64_t)uniform((int)(q0 >> 5) + u) * (2 * kBoxDim);
+      float lb = 0.0f;
+#pragma unroll
+      for (int t = 0; t < kBoxDim / 4; ++t) {
+        const float4 lo = bx[t], hi = bx[kBoxDim / 4 + t];
+        const float g0 = max3f(lo.x - qb[kBoxDim + 4 * t], qb[4 * t] - hi.x, 0.0f);
+        const float g1 = max3f(lo.y - qb[kBoxDim + 4 * t + 1], qb[4 * t + 1] - hi.y, 0.0f);
+        const float g2 = max3f(lo.z - qb[kBoxDim + 4 * t + 2], qb[4 * t + 2] - hi.z, 0.0f);
+        const float g3 = max3f(lo.w - qb[kBoxDim + 4 * t + 3], qb[4 * t + 3] - hi.w, 0.0f);
+        if constexpr (DPAD == 16)  // (kPruneBox: the gaps add up in squares)
+          lb += g0 * g0 + g1 * g1 + g2 * g2 + g3 * g3;
+        else  // (kPrunePivot: each gap is a bound)
+          lb = fmaxf(fmaxf(lb, g0), fmaxf(fmaxf(g1, g2), g3));
+      }
+      if constexpr (DPAD > 16) lb *= lb;
+      ok = ok || !(lb > lim);
+    }
+    return ok;
+  };
+  // The waves' masks combined.
+  [[maybe_unused]] auto any_wave = [&](uint64_t m) __attribute__((always_inline)) -> uint64_t {
+    if (lane == 0) wneed[par * W + wave] = m;
+    stage_barrier();
+    uint64_t v = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) v |= wneed[par * W + w];
+    par ^= 1;
+    return ((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v);
+  };
   [[maybe_unused]] auto next = [&](bool& need) __attribute__((always_inline)) -> int64_t {
     if constexpr (UR > TR) {
       // The other stages of the unit.
@@ -953,71 +998,43 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       }
     }
     while (!um) {
-      cb += cn;
-      if (cb >= nscan) {
-        need = false;
-        ucur = -1;
-        return -1;
+      if (sg < 0) {  // the home units fill the lists before the first test
+        sg = 0;
+        ubase = hs;
+        um = __ballot(lane < hn && (hs + lane) % parts == offi);
+        om = active ? um : 0;
+        continue;
       }
-      // (The home stages fill the lists before the first test.)
-      cn = cb == 0 ? (hn + stepi - 1) / stepi : 64;
-      if (cn > nscan - cb) cn = nscan - cb;
-      // Largest squared distance any of the wave's lists still admits.
-      float lim = -INFINITY;
-      if (active) {
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-          const int64_t q = q0 + 32 * u + col;
-          if (group * 32 * NQ + 32 * u + col < q_rows) {
-            const double dq = a.n64_q[q] - 2.0 * (double)thr[u];
-            lim = fmaxf(lim, (float)dq);
-          }
+      while (!sm) {
+        if (64 * sg >= nch) {
+          need = false;
+          ucur = -1;
+          return -1;
         }
+        const int j = 64 * sg + lane;
+        const int c = ch0 + j >= nch ? ch0 + j - nch : ch0 + j;
+        const float lim = limit();
+        bool ok = false;
+        if (active && j < nch) ok = needs(a.xbox + (int64_t)c * (2 * kBoxDim), lim);
+        sm = any_wave(__ballot(ok));
+        ++sg;
       }
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) lim = fmaxf(lim, __shfl_xor(lim, off, 64));
-      lim = fmaxf(lim, 0.0f) * (1.0f + 0x1p-16f);
+      int c = ch0 + 64 * (sg - 1) + (int)__builtin_ctzll(sm);
+      c = c >= nch ? c - nch : c;
+      sm &= sm - 1;
+      ubase = 64 * c;
+      const int u = ubase + lane;
+      const float lim = limit();
       bool ok = false;
-      if (active && lane < cn) {
-        const float4* bx =
-            reinterpret_cast<const float4*>(a.sbox + (int64_t)unit_at(cb + lane) * (2 * kBoxDim));
-#pragma unroll
-        for (int u = 0; u < NQ; ++u) {
-          // (Uniform address: the query box comes through the scalar cache.)
-          const int64_t sq = (q0 >> 5) + u;
-          const float* qb = a.box32 + (int64_t)__builtin_amdgcn_readfirstlane((int)sq) * (2 * kBoxDim);
-          if (group * 32 * NQ + 32 * u >= q_rows) continue;
-          float lb = 0.0f;
-#pragma unroll
-          for (int t = 0; t < kBoxDim / 4; ++t) {
-            const float4 lo = bx[t], hi = bx[kBoxDim / 4 + t];
-            const float g0 = max3f(lo.x - qb[kBoxDim + 4 * t], qb[4 * t] - hi.x, 0.0f);
-            const float g1 = max3f(lo.y - qb[kBoxDim + 4 * t + 1], qb[4 * t + 1] - hi.y, 0.0f);
-            const float g2 = max3f(lo.z - qb[kBoxDim + 4 * t + 2], qb[4 * t + 2] - hi.z, 0.0f);
-            const float g3 = max3f(lo.w - qb[kBoxDim + 4 * t + 3], qb[4 * t + 3] - hi.w, 0.0f);
-            if (a.prune == kPrunePivot) {
-              lb = fmaxf(fmaxf(lb, g0), fmaxf(fmaxf(g1, g2), g3));
-            } else {
-              lb += g0 * g0 + g1 * g1 + g2 * g2 + g3 * g3;
-            }
-          }
-          if (a.prune == kPrunePivot) lb *= lb;
-          ok = ok || !(lb > lim);
-        }
-      }
+      if (active && u < nst && (u < hs || u >= hs + hn) && (parts == 1 || u % parts == offi))
+        ok = needs(a.sbox + (int64_t)u * (2 * kBoxDim), lim);
       om = __ballot(ok);
-      if (lane == 0) wneed[par * W + wave] = om;
-      stage_barrier();
-#pragma unroll
-      for (int w = 0; w < W; ++w) um |= wneed[par * W + w];
-      um = ((uint64_t)__builtin_amdgcn_readfirstlane((int)(um >> 32)) << 32) |
-           (uint32_t)__builtin_amdgcn_readfirstlane((int)um);
-      par ^= 1;
+      um = any_wave(om);
     }
     const int bit = __builtin_ctzll(um);
     need = (om >> bit) & 1;
     um &= um - 1;
-    ucur = r_begin + (int64_t)uniform(unit_at(cb + bit)) * UR;
+    ucur = r_begin + (int64_t)uniform(ubase + bit) * UR;
     uneed = need;
     uend = ucur + UR < r_end ? ucur + UR : r_end;
     return ucur;
@@ -1227,13 +1244,13 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
 // With one reference split, those workgroups' scans are cut into P pieces on
 // P times as many workgroups (tail_pieces picks P), in a second launch whose
 // lists go to the tail region.
-template <typename ET, int DPAD, bool FOLD, int R, bool PR, int W = tile_waves(DPAD, FOLD, R),
-          int NS = stage_subs(DPAD, FOLD, R),
+template <typename ET, int DPAD, bool FOLD, int R, bool PR, int W = tile_waves(DPAD, FOLD, R, PR),
+          int NS = stage_subs(DPAD, FOLD, R, PR),
           int NG = (DPAD <= 32 ? 4 : (DPAD == 64 ? 2 : 1)), int NQ = query_groups(DPAD, FOLD, R)>
 hipError_t launch_mtile_pr(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
                         hipStream_t st, TileTail* tail) {
-  const size_t lds = lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ);
-  static_assert(lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ) <= 160 * 1024,
+  const size_t lds = lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ, PR);
+  static_assert(lds_bytes(DPAD, FOLD, W, NS, queue_slots<R, NQ>(), NQ, PR) <= 160 * 1024,
                 "LDS per workgroup");
   const auto kern = mtile_kernel<ET, DPAD, FOLD, R, W, NS, NG, NQ, PR>;
   constexpr int QW = W * 32 * NQ;  // queries per workgroup
@@ -1311,13 +1328,12 @@ hipError_t launch_mtile_pr(const Plan& p, const Args& a, int64_t q_begin, int64_
 template <typename ET, int DPAD, bool FOLD, int R>
 hipError_t launch_mtile(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
                         hipStream_t st, TileTail* tail) {
-  if constexpr (DPAD > 16)
-    if (a.prune) {
-      const hipError_t e =
-          launch_mtile_pr<ET, DPAD, FOLD, R, true>(p, a, q_begin, q_rows, st, tail);
-      // With a plan, the plain scan follows: the plan lets one of the two run.
-      if (e != hipSuccess || !a.plan) return e;
-    }
+  if (a.prune) {
+    const hipError_t e =
+        launch_mtile_pr<ET, DPAD, FOLD, R, true>(p, a, q_begin, q_rows, st, tail);
+    // With a plan, the plain scan follows: the plan lets one of the two run.
+    if (e != hipSuccess || !a.plan) return e;
+  }
   return launch_mtile_pr<ET, DPAD, FOLD, R, false>(p, a, q_begin, q_rows, st, tail);
 }
 

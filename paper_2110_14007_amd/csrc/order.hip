@@ -229,6 +229,231 @@ assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d, const Ctrl* _
                          sqrtf(acc[4 * c + 3]));
 }
 
+// ---------------------------------------------------------------------------
+// k-d order (rows of at most 16 elements with the pruned scan).  A tree of
+// medians over a sample gives up to 1024 leaves, which the counting sort lays
+// out in tree order; then every chunk of 4096 positions is split on its own
+// rows' medians down to 32, so that sub-tiles, stages and chunks of stages are
+// compact boxes.  Each split takes the dimension of the largest variance.
+// ---------------------------------------------------------------------------
+constexpr int kKdThreads = 1024;
+constexpr int kKdSamples = 8;      // sample rows per leaf
+constexpr int kKdChunk = 4096;     // rows of the local splits
+constexpr int kKdLook = 64;        // rows of a node its variances are taken from
+
+// Order-preserving bits of a float.
+__device__ __forceinline__ uint32_t ord_bits(float v) {
+  const uint32_t u = __float_as_uint(v);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// Lanes t + 16 g: variance of dimension t over the values of the lanes' rows,
+// given as each lane's count, sum and sum of squares; returns the dimension of
+// the largest one (ties to the lower one), the same in every lane.
+__device__ __forceinline__ int widest(float c, float s, float q, int d, int lane) {
+  for (int off = 16; off < 64; off <<= 1) {
+    c += __shfl_xor(c, off, 64);
+    s += __shfl_xor(s, off, 64);
+    q += __shfl_xor(q, off, 64);
+  }
+  int best = lane & 15;
+  float v = best < d && c > 0.0f ? q - s * s / c : -1.0f;
+  for (int off = 1; off < 16; off <<= 1) {
+    const float o = __shfl_xor(v, off, 64);
+    const int b = __shfl_xor(best, off, 64);
+    if (o > v || (o == v && b < best)) {
+      v = o;
+      best = b;
+    }
+  }
+  return __shfl(best < d ? best : 0, 0, 64);
+}
+
+// One pass of a bitonic sort of segments of seg entries (a power of two).
+template <typename K>
+__device__ __forceinline__ void bitonic_pass(K* key, int n, int seg, int size, int stride) {
+  for (int e = threadIdx.x; e < n / 2; e += kKdThreads) {
+    const int lo = 2 * stride * (e / stride) + (e & (stride - 1)), hi = lo + stride;
+    const bool asc = size == seg || (lo & size) == 0;
+    const K a = key[lo], b = key[hi];
+    if ((b < a) == asc && a != b) {
+      key[lo] = b;
+      key[hi] = a;
+    }
+  }
+  __syncthreads();
+}
+
+// The tree over m = kKdSamples 2^levels evenly spaced rows: node h (1 = root)
+// splits at tree[h] = (dimension, value); rows with a value >= it go right.
+// One workgroup; the keys (value, sample) of a node's samples are a segment.
+__global__ void __launch_bounds__(kKdThreads)
+kd_build_kernel(const float* __restrict__ x, int64_t n, int d, int m, int levels,
+                int2* __restrict__ tree) {
+  extern __shared__ uint64_t skey[];  // [m]
+  __shared__ int sdim[kOrdMaxC / 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto row_of = [&](uint64_t k) { return (int64_t)(uint32_t)k * n / m; };
+  for (int i = tid; i < m; i += kKdThreads) skey[i] = (uint64_t)i;
+  __syncthreads();
+  for (int l = 0; l < levels; ++l) {
+    const int seg = m >> l, nodes = 1 << l;
+    const int look = seg < kKdLook ? seg : kKdLook, step = seg / look;
+    for (int nd = wave; nd < nodes; nd += kKdThreads / 64) {
+      const int t = lane & 15;
+      float c = 0.0f, s = 0.0f, q = 0.0f;
+      if (t < d) {
+        const float r0 = x[row_of(skey[nd * seg]) * d + t];
+        for (int i = lane >> 4; i < look; i += 4) {
+          const float v = x[row_of(skey[nd * seg + i * step]) * d + t] - r0;
+          c += 1.0f;
+          s += v;
+          q = fmaf(v, v, q);
+        }
+      }
+      const int w = widest(c, s, q, d, lane);
+      if (lane == 0) sdim[nd] = w;
+    }
+    __syncthreads();
+    for (int i = tid; i < m; i += kKdThreads) {
+      const uint64_t k = skey[i];
+      skey[i] = ((uint64_t)ord_bits(x[row_of(k) * d + sdim[i / seg]]) << 32) | (uint32_t)k;
+    }
+    __syncthreads();
+    for (int size = 2; size <= seg; size <<= 1)
+      for (int stride = size >> 1; stride > 0; stride >>= 1)
+        bitonic_pass(skey, m, seg, size, stride);
+    for (int nd = tid; nd < nodes; nd += kKdThreads)
+      tree[nodes + nd] = make_int2(
+          sdim[nd],
+          __float_as_int(x[row_of(skey[nd * seg + seg / 2]) * d + sdim[nd]]));
+    __syncthreads();
+  }
+}
+
+// lab[row] = leaf of the row.
+__global__ void __launch_bounds__(kAssignThreads)
+assign_kd_kernel(const float* __restrict__ x, int64_t n, int d, int levels,
+                 const int2* __restrict__ tree, int32_t* __restrict__ lab) {
+  __shared__ int2 st[kOrdMaxC];
+  for (int i = threadIdx.x + 1; i < (1 << levels); i += kAssignThreads) st[i] = tree[i];
+  __syncthreads();
+  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (row >= n) return;
+  const float* in = x + row * d;
+  int h = 1;
+  for (int l = 0; l < levels; ++l) {
+    const int2 nd = st[h];
+    h = 2 * h + (in[nd.x] >= __int_as_float(nd.y) ? 1 : 0);
+  }
+  lab[row] = h - (1 << levels);
+}
+
+// Local splits: one workgroup per chunk of kKdChunk positions, 4096 to 32 rows
+// in seven levels.  The rows' values sit in LDS as fp16 (scaled and centred
+// as for the quantisation; only the order matters), a key is (far flag, value,
+// local row).  Rows more than kKdFar times the chunk's mean squared distance
+// from its mean are flagged and end up last in the chunk, so that a few far
+// rows widen the boxes of the last sub-tiles only.
+constexpr float kKdFar = 5.0f;
+
+__global__ void __launch_bounds__(kKdThreads)
+kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __restrict__ mu32,
+                const Ctrl* __restrict__ ctrl, int scale_exp, int32_t* __restrict__ perm) {
+  extern __shared__ uint32_t lkey[];  // [kKdChunk], then the values [d][kKdChunk]
+  _Float16* const val = reinterpret_cast<_Float16*>(lkey + kKdChunk);
+  __shared__ int sdim[kKdChunk / 64];
+  __shared__ float smean[16], red[kKdThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t base = (int64_t)blockIdx.x * kKdChunk;
+  const int rows = n - base < kKdChunk ? (int)(n - base) : kKdChunk;
+  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
+  constexpr int kPer = kKdChunk / kKdThreads;
+  int32_t mine[kPer];
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid + e * kKdThreads;
+    mine[e] = i < rows ? perm[base + i] : 0;
+    for (int t = 0; t < d; ++t)
+      val[t * kKdChunk + i] =
+          i < rows ? (_Float16)((x[(int64_t)mine[e] * d + t] - mu32[t]) * sc) : (_Float16)0.0f;
+  }
+  __syncthreads();
+  if (wave < d) {
+    float s = 0.0f;
+    for (int i = lane; i < rows; i += 64) s += (float)val[wave * kKdChunk + i];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) smean[wave] = s / (float)rows;
+  }
+  __syncthreads();
+  float dist[kPer], tot = 0.0f;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid + e * kKdThreads;
+    dist[e] = 0.0f;
+    for (int t = 0; t < d; ++t) {
+      const float df = (float)val[t * kKdChunk + i] - smean[t];
+      dist[e] = fmaf(df, df, dist[e]);
+    }
+    tot += i < rows ? dist[e] : 0.0f;
+  }
+  for (int off = 32; off > 0; off >>= 1) tot += __shfl_xor(tot, off, 64);
+  if (lane == 0) red[wave] = tot;
+  __syncthreads();
+  tot = 0.0f;
+  for (int w = 0; w < kKdThreads / 64; ++w) tot += red[w];
+  constexpr uint32_t kFar = 1u << 28, kNone = 1u << 29;  // flags above value << 12 | row
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid + e * kKdThreads;
+    lkey[i] = (uint32_t)i | (i >= rows ? kNone : dist[e] * (float)rows > kKdFar * tot ? kFar : 0u);
+  }
+  __syncthreads();
+  for (int seg = kKdChunk; seg > 32; seg >>= 1) {
+    const int nodes = kKdChunk / seg;
+    constexpr int look = kKdLook;
+    const int step = seg / look;
+    for (int nd = wave; nd < nodes; nd += kKdThreads / 64) {
+      const int t = lane & 15;
+      float c = 0.0f, s = 0.0f, q = 0.0f;
+      if (t < d)
+        for (int i = lane >> 4; i < look; i += 4) {
+          const uint32_t k = lkey[nd * seg + i * step];
+          if (k >= kFar) continue;
+          const float v = ((float)val[t * kKdChunk + (k & (kKdChunk - 1))] - smean[t]) * 0x1p-14f;
+          c += 1.0f;
+          s += v;
+          q = fmaf(v, v, q);
+        }
+      const int w = widest(c, s, q, d, lane);
+      if (lane == 0) sdim[nd] = w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const int i = tid + e * kKdThreads;
+      const uint32_t k = lkey[i], r = k & (kKdChunk - 1);
+      const uint16_t hb = __builtin_bit_cast(uint16_t, val[sdim[i / seg] * kKdChunk + r]);
+      const uint32_t code = (uint16_t)((hb & 0x8000u) ? ~hb : (hb | 0x8000u));
+      lkey[i] = (k & (kFar | kNone)) | (code << 12) | r;
+    }
+    __syncthreads();
+    for (int size = 2; size <= seg; size <<= 1)
+      for (int stride = size >> 1; stride > 0; stride >>= 1)
+        bitonic_pass(lkey, kKdChunk, seg, size, stride);
+  }
+  // (Every row of the chunk is in a register: they change places through LDS.)
+  int32_t* const out = reinterpret_cast<int32_t*>(val);
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) out[tid + e * kKdThreads] = mine[e];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid + e * kKdThreads;
+    if (i < rows) perm[base + i] = out[lkey[i] & (kKdChunk - 1)];
+  }
+}
+
 // Rows per group in each block of kOrdRows rows.
 __global__ void __launch_bounds__(256)
 count_kernel(const int32_t* __restrict__ lab, int64_t n, int G, int32_t* __restrict__ bcnt) {
@@ -386,7 +611,33 @@ pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ pe
   if (t == 0) substart[sub] = kstart[lab[perm[r0]]];
 }
 
-// Boxes of the stages (nsub sub-tiles each) from those of their sub-tiles.
+// Boxes of the quantised columns of the 32-row sub-tiles (exact values).
+template <typename T>
+__global__ void __launch_bounds__(kSubsPerBlock * kBoxDim)
+column_box_kernel(const T* __restrict__ xq, int64_t n, int64_t subs, int d, int dpad,
+                  float* __restrict__ box32, int32_t* __restrict__ substart) {
+  const int t = threadIdx.x & (kBoxDim - 1);
+  const int64_t sub = (int64_t)blockIdx.x * kSubsPerBlock + (threadIdx.x / kBoxDim);
+  if (sub >= subs) return;
+  const int64_t r0 = 32 * sub;
+  const int rows = n - r0 < 32 ? (int)(n - r0) : 32;
+  float lo = 0.0f, hi = 0.0f;
+  if (t < d) {
+    lo = hi = (float)xq[r0 * dpad + t];
+#pragma unroll 8
+    for (int i = 1; i < rows; ++i) {
+      const float v = (float)xq[(r0 + i) * dpad + t];
+      lo = fminf(lo, v);
+      hi = fmaxf(hi, v);
+    }
+  }
+  box32[sub * (2 * kBoxDim) + t] = lo;
+  box32[sub * (2 * kBoxDim) + kBoxDim + t] = hi;
+  if (t == 0) substart[sub] = (int32_t)r0;
+}
+
+// Boxes of the stages (nsub sub-tiles each) from those of their sub-tiles, and
+// of chunks of stages from those of the stages.
 __global__ void __launch_bounds__(256)
 stage_box_kernel(const float* __restrict__ box32, int64_t subs, int64_t stages, int nsub,
                  float* __restrict__ sbox) {
@@ -648,7 +899,19 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
   const int nb = order_blocks(n);
   const int G = p.groups;
   const unsigned ga = (unsigned)((n + kAssignThreads - 1) / kAssignThreads);
-  if (p.d <= kSmallD) {
+  if (p.prune == kPruneBox) {
+    int levels = 0;
+    while ((1 << levels) < G) ++levels;
+    const int m = kKdSamples << levels;
+    const size_t lds = sizeof(uint64_t) * (size_t)m;
+    hipError_t e = hipFuncSetAttribute((const void*)kd_build_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kd_build_kernel, dim3(1), dim3(kKdThreads), lds, st, a.xr, n, (int)p.d, m,
+                       levels, reinterpret_cast<int2*>(a.oseed));
+    hipLaunchKernelGGL(assign_kd_kernel, dim3(ga), dim3(kAssignThreads), 0, st, a.xr, n, (int)p.d,
+                       levels, reinterpret_cast<const int2*>(a.oseed), a.lab);
+  } else if (p.d <= kSmallD) {
     const int DT = (int)((p.d + 3) & ~3);
     hipLaunchKernelGGL(seeds_kernel, dim3((unsigned)((G * DT + 255) / 256)), dim3(256), 0, st,
                        a.xr, n, (int)p.d, G, DT, a.oseed);
@@ -690,18 +953,48 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
   while ((1 << bits) < G) ++bits;
   hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nb), dim3(64), 0, st, a.lab, n, G, bits,
                      a.boff, a.cstart, a.perm);
+  if (p.prune == kPruneBox) {
+    const size_t lds = sizeof(uint32_t) * kKdChunk + sizeof(_Float16) * kKdChunk *
+                                                         (size_t)(p.d < 2 ? 2 : p.d);
+    hipError_t e = hipFuncSetAttribute((const void*)kd_local_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kd_local_kernel, dim3((unsigned)((n + kKdChunk - 1) / kKdChunk)),
+                       dim3(kKdThreads), lds, st, a.xr, n, (int)p.d, a.mu32, a.ctrl, p.scale_exp,
+                       a.perm);
+  }
   return hipGetLastError();
+}
+
+// Leaves of the k-d order's tree: chunks of the local splits hold about one.
+int32_t kd_leaves(int64_t nr) {
+  int32_t g = 2;
+  while (g < kOrdMaxC && (int64_t)g * kKdChunk < nr) g *= 2;
+  return g;
 }
 
 hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t st) {
   const int64_t subs = p.nr_pad / 32;
   const int64_t stages = (p.nr + p.stage_rows - 1) / p.stage_rows;
-  const float eps = (float)(p.d + 16) * 0x1p-24f;
-  hipLaunchKernelGGL(pivot_box_kernel, dim3((unsigned)((subs + kSubsPerBlock - 1) / kSubsPerBlock)),
-                     dim3(kSubsPerBlock * kBoxDim), 0, st, a.pdist, a.perm, a.lab, a.kstart, p.nr,
-                     subs, eps, a.ctrl, a.box32, a.substart);
-  hipLaunchKernelGGL(stage_box_kernel, dim3((unsigned)((stages * 2 * kBoxDim + 255) / 256)),
-                     dim3(256), 0, st, a.box32, subs, stages, p.stage_rows / 32, a.sbox);
+  const unsigned gsub = (unsigned)((subs + kSubsPerBlock - 1) / kSubsPerBlock);
+  const dim3 bsub(kSubsPerBlock * kBoxDim);
+  if (p.prune == kPrunePivot) {
+    const float eps = (float)(p.d + 16) * 0x1p-24f;
+    hipLaunchKernelGGL(pivot_box_kernel, dim3(gsub), bsub, 0, st, a.pdist, a.perm, a.lab, a.kstart,
+                       p.nr, subs, eps, a.ctrl, a.box32, a.substart);
+  } else if (p.precision == TOD_PREC_FP16) {
+    hipLaunchKernelGGL(column_box_kernel<_Float16>, dim3(gsub), bsub, 0, st,
+                       (const _Float16*)a.xq_r, p.nr, subs, (int)p.d, p.dpad, a.box32, a.substart);
+  } else {
+    hipLaunchKernelGGL(column_box_kernel<__bf16>, dim3(gsub), bsub, 0, st, (const __bf16*)a.xq_r,
+                       p.nr, subs, (int)p.d, p.dpad, a.box32, a.substart);
+  }
+  const auto grid = [](int64_t boxes) { return dim3((unsigned)((boxes * 2 * kBoxDim + 255) / 256)); };
+  const int64_t chunks = (stages + 63) / 64;
+  hipLaunchKernelGGL(stage_box_kernel, grid(stages), dim3(256), 0, st, a.box32, subs, stages,
+                     p.stage_rows / 32, a.sbox);
+  hipLaunchKernelGGL(stage_box_kernel, grid(chunks), dim3(256), 0, st, a.sbox, stages, chunks, 64,
+                     a.xbox);
   return hipGetLastError();
 }
 

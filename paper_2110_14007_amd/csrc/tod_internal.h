@@ -93,7 +93,7 @@ inline int tail_pieces(int64_t tw, int64_t slots, int64_t cus, int pmax, bool au
 struct Layout {
   size_t ctrl, mu64, mu32, colpart, xq_r, xq_q, hn_r, n64_q, rho_q, partial, ptail, worklist,
       fbtau, fbpart, fbidx, idx32, d64, lrd, kdist, perm, lab, oseed, cstart, bcnt, boff,
-      kstart, box32, sbox, substart, plan, total;
+      kstart, box32, sbox, xbox, substart, plan, total;
   int32_t colpart_blocks;
 };
 
@@ -180,6 +180,7 @@ struct Args {
                        // (lies over the partial lists: dead once the boxes are made)
   float* box32;        // boxes of the 32-row sub-tiles [nr_pad / 32][2 kBoxDim]: lo, hi
   float* sbox;         // boxes of the stages [ceil(nr / stage_rows)][2 kBoxDim]
+  float* xbox;         // boxes of chunks of 64 stages
   int32_t* substart;   // per sub-tile: position where its scan starts after the home stages
   int32_t* plan;       // work plan of a launch (plan_words): extra pieces and the tiles' pieces
   int64_t plan_tiles;  // first word of the plan's per-tile records
@@ -290,6 +291,7 @@ __device__ __forceinline__ RowLists row_lists(const Args& a, int64_t ql) {
   return r;
 }
 int32_t order_groups(int64_t nr, int64_t d);
+int32_t kd_leaves(int64_t nr);  // keys of the k-d order (kPruneBox)
 int32_t order_blocks(int64_t nr);
 hipError_t launch_order(const Plan& p, const Args& a, hipStream_t s);
 

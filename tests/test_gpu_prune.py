@@ -55,6 +55,17 @@ def data(kind, n, d, rng):
     ("uniform", 33333, 70, 20, {}),
     ("shells", 24007, 24, 15, {}),
     ("two", 16999, 30, 7, {}),
+    # rows of at most 16 elements: boxes of the columns in k-d order; the folded row
+    # (d <= 8) and the plain one, one chunk of local splits and several, a last chunk of
+    # one row
+    ("clusters", 20481, 8, 5, {}),
+    ("uniform", 50000, 3, 20, {"precision": "bf16"}),
+    ("uniform", 40000, 8, 5, {"query_block": 4096}),
+    ("clusters", 30011, 11, 40, {}),
+    ("shells", 24577, 16, 5, {}),
+    ("two", 21000, 1, 3, {}),
+    ("two", 21000, 5, 20, {}),
+    ("clusters", 70, 5, 4, {"ref_splits": 1}),
 ])
 def test_pruned_equals_plain(env, kind, n, d, k, opt):
     torch, tod, oracle = env
