@@ -92,10 +92,28 @@ tod_status check_sizes(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t exc
 namespace tod {
 
 // Reference splits for a query block of qb rows (Section 6 customised cdist
-// batching): enough waves for two per SIMD on 256 CUs x 4 SIMDs, but at
-// least 2048 references per split (every split keeps its own K' list per
-// query, so splits cost selection work), and at most 16.
-int64_t auto_splits(int64_t qb, int64_t nr) {
+// batching): enough waves for two per SIMD on 256 CUs x 4 SIMDs (one per SIMD
+// with lists of 64 entries and more, whose kernels hold one), rounded down so
+// that no second round of workgroups follows, but at least 8 K' references per
+// split, and at most 64.  Every split fills its own K' list per query, but while
+// the GPU has idle compute units that runs beside the other splits: what counts
+// is the length of one wave's scan.  (At 2,000 x 16, k = 10, the tile takes 54 us
+// in seven splits, 82 in one; 64 queries against 50,000 x 32 took 145 us in the
+// 16 splits that 2,048 rows each allowed.)
+int64_t auto_splits(int64_t qb, int64_t nr, int64_t kp) {
+  // (In workgroups of four waves.)
+  const int64_t groups = (qb + 127) / 128, target = kp >= 64 ? 256 : 512;
+  int64_t s = target / groups;
+  if (s < 2) s = (target + groups - 1) / groups;
+  const int64_t cap = nr / (8 * kp) > 1 ? nr / (8 * kp) : 1;
+  if (s > cap) s = cap;
+  if (s > 64) s = 64;
+  return s < 1 ? 1 : s;
+}
+
+// Splits of a range query (no lists to fill): two waves per SIMD, at least
+// 2048 references each, at most 16.
+static int64_t nwr_splits(int64_t qb, int64_t nr) {
   const int64_t waves = (qb + 31) / 32;
   int64_t s = (2048 + waves - 1) / waves;
   const int64_t cap = nr / 2048 > 1 ? nr / 2048 : 1;
@@ -182,7 +200,7 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
                       prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
                       (nr >= kPruneMinRows || o.reorder > 0);
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr));
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr, kp));
   p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
   // operand fits in registers and whose shortlist is 16, 32 or 64 long.  Rows
@@ -385,9 +403,9 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
       if (qb > f.nq_pad) qb = f.nq_pad;
       if (qb < kPruneMinBlock && qb < f.nq_pad) continue;
       f.query_block = qb;
-      if (auto_splits(qb, f.nr) != 1 || make_layout(f).total > ws_bytes) continue;
+      if (auto_splits(qb, f.nr, f.kprime) != 1 || make_layout(f).total > ws_bytes) continue;
     }
-    int64_t s = auto_splits(qb, f.nr);
+    int64_t s = auto_splits(qb, f.nr, f.kprime);
     const int64_t smax = (int64_t)(room / ((size_t)qb * per));
     if (s > smax) s = smax;
     f.query_block = qb;
@@ -436,7 +454,7 @@ tod_status make_plan_nwr(int64_t nq, int64_t nr, int64_t d, int32_t self, const 
   p->nr_pad = round_up(nr, 32);
   p->query_block = p->nq_pad;
   p->blocks = 1;
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits : auto_splits(p->nq_pad, nr));
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits : nwr_splits(p->nq_pad, nr));
   p->waves_per_group = 4;
   p->tile_kind = 2;
   return TOD_OK;

@@ -316,8 +316,11 @@ __device__ __forceinline__ int swz(int r) { return ((r >> 2) ^ (r >> 3)) & 1; }
 // stages ahead (three buffers) for waves of 32 queries and one stage ahead
 // (two buffers, stages twice as long) for waves of 64; other rows through
 // registers (two buffers).
-__host__ __device__ constexpr int stage_buffers(int dpad, bool fold, int nq) {
-  return dpad >= 512 && !fold && nq == 1 ? 3 : 2;
+// The pruned scan of folded rows (short stages, few waves of which need any
+// one) stages directly too, two stages ahead: with one ahead in registers the
+// load latency bound it (1.3 us a stage of 128 rows at 4 10^6 rows of 8).
+__host__ __device__ constexpr int stage_buffers(int dpad, bool fold, int nq, bool pr) {
+  return (dpad >= 512 && !fold && nq == 1) || (fold && pr) ? 3 : 2;
 }
 
 // Queue slots per lane and query group (two groups: 16 slots, the LDS of two
@@ -328,8 +331,8 @@ constexpr int queue_slots() { return NQ == 1 ? queue_cap<R>() : 16; }
 // Stage buffers, their seeds, the queues and the pruned scan's stage masks.
 __host__ __device__ constexpr size_t lds_bytes(int dpad, bool fold, int w, int ns, int qcap,
                                                int nq, bool pr) {
-  return (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * (dpad == 16 ? 32 : dpad * 2 + 16) +
-         (fold ? 0 : (size_t)stage_buffers(dpad, fold, nq) * 32 * ns * sizeof(uint2)) +
+  return (size_t)stage_buffers(dpad, fold, nq, pr) * 32 * ns * (dpad == 16 ? 32 : dpad * 2 + 16) +
+         (fold ? 0 : (size_t)stage_buffers(dpad, fold, nq, pr) * 32 * ns * sizeof(uint2)) +
          (size_t)w * nq * qcap * 64 * sizeof(uint2) +
          (pr ? (size_t)2 * w * sizeof(uint64_t) : 0);
 }
@@ -373,7 +376,8 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   constexpr int NL = (CHUNKS + NT - 1) / NT;
   static_assert(NL <= 16, "staged chunks per thread");
   constexpr bool DL = DPAD >= 512 && !FOLD;  // direct staging
-  constexpr int NBUF = stage_buffers(DPAD, FOLD, NQ);
+  constexpr int NBUF = stage_buffers(DPAD, FOLD, NQ, PR);
+  constexpr bool DLF = FOLD && PR;  // direct staging of folded rows
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* stage = smem;
   uint2* hnb = (uint2*)(smem + NBUF * STAGE);  // plain layout: seed parts of the staged rows
@@ -479,9 +483,9 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // two register sets with fixed roles; shorter rows one stage ahead.
   constexpr bool PF2 = DPAD >= 256 && !DL;
   const unsigned char* xr_bytes = (const unsigned char*)a.xq_r;
-  uint4 st[DL ? 1 : NL], su[PF2 ? NL : 1];
+  uint4 st[DL || DLF ? 1 : NL], su[PF2 ? NL : 1];
 #pragma unroll
-  for (int i = 0; i < (DL ? 1 : NL); ++i) st[i] = make_uint4(0, 0, 0, 0);
+  for (int i = 0; i < (DL || DLF ? 1 : NL); ++i) st[i] = make_uint4(0, 0, 0, 0);
 #pragma unroll
   for (int i = 0; i < (PF2 ? NL : 1); ++i) su[i] = make_uint4(0, 0, 0, 0);
   static_assert(TR / 2 <= NT, "the seed parts of two rows per thread");
@@ -1120,6 +1124,46 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
         dl_barrier<0>();
       }
     }
+    }
+    // No staging write may outlive the workgroup's LDS allocation.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else if constexpr (DLF) {
+    // Folded rows: 32 rows (1 KiB) an instruction, spread over the waves; a lane fetches the half its LDS place holds (swz).  Rows past the
+    // padded end repeat the last one and are never read back.
+    constexpr int LPW = TR / 32 > W ? TR / 32 / W : 1;  // staging loads per wave and stage
+    static_assert(TR / 32 <= W || (TR / 32) % W == 0, "staging loads spread evenly");
+    const int lrow = lane >> 1;
+    const int lhalf = ((lane & 1) ^ swz(lrow)) * 16;
+    auto issue = [&](int64_t t0, int b) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < LPW; ++i) {
+        const int part = wv + W * i;  // 32 rows
+        if (part < TR / 32) {
+          const int64_t row = t0 + 32 * part + lrow;
+          dma16(xr_bytes + (row < r_end32 ? row : r_end32 - 1) * 32 + lhalf,
+                lbase + b * STAGE + part * 1024);
+        }
+      }
+    };
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the query operand's loads
+    bool n0, n1, n2;
+    int64_t t0 = next(n0);
+    const int64_t td = t0 < 0 ? r_begin : t0;
+    int64_t t1 = next(n1);
+    issue(td, 0);
+    issue(t1 < 0 ? td : t1, 1);
+    dl_barrier<LPW>();
+    for (int b = 0; t0 >= 0;) {
+      // Buffer b + 2 (mod 3) was last read in the previous trip, before its barrier.
+      const int64_t t2 = next(n2);
+      issue(t2 < 0 ? td : t2, b == 0 ? 2 : b - 1);
+      if (n0) stage_body(t0, b);
+      dl_barrier<LPW>();
+      t0 = t1;
+      n0 = n1;
+      t1 = t2;
+      n1 = n2;
+      b = b == 2 ? 0 : b + 1;
     }
     // No staging write may outlive the workgroup's LDS allocation.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");

@@ -13,7 +13,7 @@ constexpr int kUnitRows = 128;
 
 // Waves per workgroup.
 constexpr int tile_waves(int dpad, bool fold, int r, bool pr) {
-  return fold && r <= 8 ? (pr ? 8 : 16) : (dpad == 64 && !fold && r == 16) ? 8 : 4;
+  return fold && r <= 8 ? (pr ? 4 : 16) : (dpad == 64 && !fold && r == 16) ? 8 : 4;
 }
 // 32-row sub-tiles per stage: the stage pair, seeds and queues of a 4-wave
 // workgroup stay under 80 KiB so that at least two workgroups share a CU.

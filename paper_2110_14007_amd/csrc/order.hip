@@ -232,13 +232,13 @@ assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d, const Ctrl* _
 // ---------------------------------------------------------------------------
 // k-d order (rows of at most 16 elements with the pruned scan).  A tree of
 // medians over a sample gives up to 1024 leaves, which the counting sort lays
-// out in tree order; then every chunk of 4096 positions is split on its own
+// out in tree order; then every chunk of 1024 or 4096 positions is split on its own
 // rows' medians down to 32, so that sub-tiles, stages and chunks of stages are
 // compact boxes.  Each split takes the dimension of the largest variance.
 // ---------------------------------------------------------------------------
 constexpr int kKdThreads = 1024;
-constexpr int kKdSamples = 8;      // sample rows per leaf
-constexpr int kKdChunk = 4096;     // rows of the local splits
+constexpr int kKdSamples = 4;      // sample rows per leaf
+constexpr int kKdChunkMost = 4096;  // rows of the local splits (fewer: 1024, see kd_chunk)
 constexpr int kKdLook = 64;        // rows of a node its variances are taken from
 
 // Order-preserving bits of a float.
@@ -269,18 +269,32 @@ __device__ __forceinline__ int widest(float c, float s, float q, int d, int lane
   return __shfl(best < d ? best : 0, 0, 64);
 }
 
-// One pass of a bitonic sort of segments of seg entries (a power of two).
+// Bitonic sort of segments of 2^lseg entries.  (A pass whose pairs lie within
+// the 128 entries one wave handles needs no workgroup barrier.)
 template <typename K>
-__device__ __forceinline__ void bitonic_pass(K* key, int n, int seg, int size, int stride) {
-  for (int e = threadIdx.x; e < n / 2; e += kKdThreads) {
-    const int lo = 2 * stride * (e / stride) + (e & (stride - 1)), hi = lo + stride;
-    const bool asc = size == seg || (lo & size) == 0;
-    const K a = key[lo], b = key[hi];
-    if ((b < a) == asc && a != b) {
-      key[lo] = b;
-      key[hi] = a;
+__device__ __forceinline__ void bitonic_segments(K* key, int n, int lseg) {
+  for (int lsize = 1; lsize <= lseg; ++lsize)
+    for (int ls = lsize - 1; ls >= 0; --ls) {
+      for (int e = threadIdx.x; e < n / 2; e += kKdThreads) {
+        const int lo = ((e >> ls) << (ls + 1)) | (e & ((1 << ls) - 1)), hi = lo + (1 << ls);
+        const bool asc = lsize == lseg || ((lo >> lsize) & 1) == 0;
+        const K a = key[lo], b = key[hi];
+        if ((b < a) == asc && a != b) {
+          key[lo] = b;
+          key[hi] = a;
+        }
+      }
+      // Strides up to 64 stay within a wave's 128 consecutive entries; the next
+      // pass's stride is smaller, or (at ls = 0) as large as the segments grow.
+      const int next = ls > 0 ? ls - 1 : lsize;
+      if (ls > 6 || next > 6) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      }
     }
-  }
   __syncthreads();
 }
 
@@ -317,12 +331,11 @@ kd_build_kernel(const float* __restrict__ x, int64_t n, int d, int m, int levels
     __syncthreads();
     for (int i = tid; i < m; i += kKdThreads) {
       const uint64_t k = skey[i];
-      skey[i] = ((uint64_t)ord_bits(x[row_of(k) * d + sdim[i / seg]]) << 32) | (uint32_t)k;
+      skey[i] = ((uint64_t)ord_bits(x[row_of(k) * d + sdim[i >> __builtin_ctz(seg)]]) << 32) |
+                (uint32_t)k;
     }
     __syncthreads();
-    for (int size = 2; size <= seg; size <<= 1)
-      for (int stride = size >> 1; stride > 0; stride >>= 1)
-        bitonic_pass(skey, m, seg, size, stride);
+    bitonic_segments(skey, m, __builtin_ctz(seg));
     for (int nd = tid; nd < nodes; nd += kKdThreads)
       tree[nodes + nd] = make_int2(
           sdim[nd],
@@ -349,14 +362,14 @@ assign_kd_kernel(const float* __restrict__ x, int64_t n, int d, int levels,
   lab[row] = h - (1 << levels);
 }
 
-// Local splits: one workgroup per chunk of kKdChunk positions, 4096 to 32 rows
-// in seven levels.  The rows' values sit in LDS as fp16 (scaled and centred
+// Local splits: one workgroup per chunk of kKdChunk positions, down to 32 rows.  The rows' values sit in LDS as fp16 (scaled and centred
 // as for the quantisation; only the order matters), a key is (far flag, value,
 // local row).  Rows more than kKdFar times the chunk's mean squared distance
 // from its mean are flagged and end up last in the chunk, so that a few far
 // rows widen the boxes of the last sub-tiles only.
 constexpr float kKdFar = 5.0f;
 
+template <int kKdChunk>
 __global__ void __launch_bounds__(kKdThreads)
 kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __restrict__ mu32,
                 const Ctrl* __restrict__ ctrl, int scale_exp, int32_t* __restrict__ perm) {
@@ -410,9 +423,9 @@ kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __re
   }
   __syncthreads();
   for (int seg = kKdChunk; seg > 32; seg >>= 1) {
-    const int nodes = kKdChunk / seg;
+    const int lseg = __builtin_ctz(seg), nodes = kKdChunk >> lseg;
     constexpr int look = kKdLook;
-    const int step = seg / look;
+    const int step = seg >> 6;  // seg / look
     for (int nd = wave; nd < nodes; nd += kKdThreads / 64) {
       const int t = lane & 15;
       float c = 0.0f, s = 0.0f, q = 0.0f;
@@ -433,14 +446,12 @@ kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __re
     for (int e = 0; e < kPer; ++e) {
       const int i = tid + e * kKdThreads;
       const uint32_t k = lkey[i], r = k & (kKdChunk - 1);
-      const uint16_t hb = __builtin_bit_cast(uint16_t, val[sdim[i / seg] * kKdChunk + r]);
+      const uint16_t hb = __builtin_bit_cast(uint16_t, val[sdim[i >> lseg] * kKdChunk + r]);
       const uint32_t code = (uint16_t)((hb & 0x8000u) ? ~hb : (hb | 0x8000u));
       lkey[i] = (k & (kFar | kNone)) | (code << 12) | r;
     }
     __syncthreads();
-    for (int size = 2; size <= seg; size <<= 1)
-      for (int stride = size >> 1; stride > 0; stride >>= 1)
-        bitonic_pass(lkey, kKdChunk, seg, size, stride);
+    bitonic_segments(lkey, kKdChunk, lseg);
   }
   // (Every row of the chunk is in a register: they change places through LDS.)
   int32_t* const out = reinterpret_cast<int32_t*>(val);
@@ -954,22 +965,26 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
   hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)nb), dim3(64), 0, st, a.lab, n, G, bits,
                      a.boff, a.cstart, a.perm);
   if (p.prune == kPruneBox) {
-    const size_t lds = sizeof(uint32_t) * kKdChunk + sizeof(_Float16) * kKdChunk *
-                                                         (size_t)(p.d < 2 ? 2 : p.d);
-    hipError_t e = hipFuncSetAttribute((const void*)kd_local_kernel,
+    const int chunk = kd_chunk(n);
+    const size_t lds = (size_t)chunk * (sizeof(uint32_t) + sizeof(_Float16) * (p.d < 2 ? 2 : p.d));
+    const auto kern = chunk == kKdChunkMost ? kd_local_kernel<kKdChunkMost> : kd_local_kernel<1024>;
+    hipError_t e = hipFuncSetAttribute((const void*)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kd_local_kernel, dim3((unsigned)((n + kKdChunk - 1) / kKdChunk)),
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + chunk - 1) / chunk)),
                        dim3(kKdThreads), lds, st, a.xr, n, (int)p.d, a.mu32, a.ctrl, p.scale_exp,
                        a.perm);
   }
   return hipGetLastError();
 }
 
-// Leaves of the k-d order's tree: chunks of the local splits hold about one.
+// Rows of the local splits: as few as the tree's 1024 leaves allow.
+int kd_chunk(int64_t nr) { return nr <= (int64_t)1024 * kOrdMaxC ? 1024 : kKdChunkMost; }
+
+// Leaves of the k-d order's tree: one per chunk of the local splits.
 int32_t kd_leaves(int64_t nr) {
   int32_t g = 2;
-  while (g < kOrdMaxC && (int64_t)g * kKdChunk < nr) g *= 2;
+  while (g < kOrdMaxC && (int64_t)g * kd_chunk(nr) < nr) g *= 2;
   return g;
 }
 

@@ -248,16 +248,25 @@ recheck_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       list[r] = e < KP ? rl.first[e] : kEmpty;
     }
     sort_runs(list);
-    for (int s = 1; s < rl.n; ++s) {
-      const uint64_t* src = rl.rest + (int64_t)(s - 1) * rl.stride;
-      uint64_t other[EL];
+    // (Four lists' entries are loaded at once.)
+    constexpr int kAhead = 4;
+    for (int s0 = 1; s0 < rl.n; s0 += kAhead) {
+      uint64_t other[kAhead][EL];
 #pragma unroll
-      for (int r = 0; r < EL; ++r) {
-        const int e = r * 64 + lane;
-        other[r] = e < KP ? src[e] : kEmpty;
+      for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+        for (int r = 0; r < EL; ++r) {
+          const int e = r * 64 + lane;
+          other[i][r] = e < KP && s0 + i < rl.n
+                            ? rl.rest[(int64_t)(s0 + i - 1) * rl.stride + e]
+                            : kEmpty;
+        }
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+        if (s0 + i >= rl.n) break;  // uniform per wave
+        sort_runs(other[i]);
+        merge_lists<EL>(list, other[i], lane);
       }
-      sort_runs(other);
-      merge_lists<EL>(list, other, lane);
     }
 #pragma unroll
     for (int r = 0; r < EL; ++r) {
@@ -425,12 +434,23 @@ recheck_lanes_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     int nlw = rl.n;
 #pragma unroll
     for (int off = KP; off < 64; off <<= 1) nlw = max(nlw, __shfl_xor(nlw, off, 64));
-    for (int s = 1; s < nlw; ++s) {
-      v = umin64(v, s < rl.n ? rl.rest[(int64_t)(s - 1) * rl.stride + (KP - 1 - g)] : kEmpty);
+    // (Eight lists' entries are loaded at once: one load's latency each made 16
+    // lists of 64 queries take 15 us.)
+    constexpr int kAhead = 8;
+    for (int s0 = 1; s0 < nlw; s0 += kAhead) {
+      uint64_t w[kAhead];
 #pragma unroll
-      for (int st = KP / 2; st > 0; st >>= 1) {
-        const uint64_t o = lane_xor64(v, st);
-        v = (g & st) ? umax64(v, o) : umin64(v, o);
+      for (int i = 0; i < kAhead; ++i)
+        w[i] = s0 + i < rl.n ? rl.rest[(int64_t)(s0 + i - 1) * rl.stride + (KP - 1 - g)] : kEmpty;
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) {
+        if (s0 + i >= nlw) break;  // uniform
+        v = umin64(v, w[i]);
+#pragma unroll
+        for (int st = KP / 2; st > 0; st >>= 1) {
+          const uint64_t o = lane_xor64(v, st);
+          v = (g & st) ? umax64(v, o) : umin64(v, o);
+        }
       }
     }
     // Every reference outside the list has a key >= the K'-th key.

@@ -292,6 +292,7 @@ __device__ __forceinline__ RowLists row_lists(const Args& a, int64_t ql) {
 }
 int32_t order_groups(int64_t nr, int64_t d);
 int32_t kd_leaves(int64_t nr);  // keys of the k-d order (kPruneBox)
+int kd_chunk(int64_t nr);       // rows of its local splits
 int32_t order_blocks(int64_t nr);
 hipError_t launch_order(const Plan& p, const Args& a, hipStream_t s);
 
