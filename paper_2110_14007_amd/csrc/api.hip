@@ -111,9 +111,10 @@ int64_t auto_splits(int64_t qb, int64_t nr, int64_t kp) {
   return s < 1 ? 1 : s;
 }
 
-// Splits of a range query (no lists to fill): two waves per SIMD, at least
-// 2048 references each, at most 16.
-static int64_t nwr_splits(int64_t qb, int64_t nr) {
+// Splits of a range query (no lists to fill), and of a caller's query block whose
+// workspace is too small for auto_splits: two waves per SIMD, at least 2048
+// references each, at most 16.
+static int64_t long_splits(int64_t qb, int64_t nr) {
   const int64_t waves = (qb + 31) / 32;
   int64_t s = (2048 + waves - 1) / waves;
   const int64_t cap = nr / 2048 > 1 ? nr / 2048 : 1;
@@ -136,6 +137,30 @@ static void set_prune(Plan* p, int32_t kind) {
   p->groups = kind == kPrunePivot ? kPivots * kRadBins
               : kind == kPruneBox ? kd_leaves(p->nr)
                                   : order_groups(p->nr, p->d);
+}
+
+// What follows from the splits: the grouped order, the pruned scan, the tail split.
+static void set_order_tail(Plan* p, const tod_options& o) {
+  // Grouped scan order: X against X through the register-list kernel with one
+  // reference split (each workgroup then scans the whole set from its own
+  // group on); by default from kOrderMinRows references on.
+  const bool want = o.reorder > 0 || (o.reorder == 0 && p->nr >= kOrderMinRows);
+  // (With runs, the tile scans the whole set in pieces whatever S is.)
+  p->order = (p->self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
+  // Pruned scan: wherever the grouped order applies (its boxes cost 4 bytes
+  // a row and a stage test per 64 stages).
+  set_prune(p, !p->order ? kPruneNone : p->d > kBoxDim ? kPrunePivot : kPruneBox);
+  // Tail split of the register-list tile with one reference split (not with
+  // runs: their pieces already halve every workgroup's scan).
+  p->tail_parts = 1;
+  p->tail_auto = 0;
+  p->tail_lists = 0;
+  if (p->tile_kind == 1 && p->splits == 1 && p->runs == 1 && o.tail_parts != 1) {
+    p->tail_parts = o.tail_parts == 0 ? kMaxTailParts : o.tail_parts;
+    p->tail_auto = o.tail_parts == 0 ? 1 : 0;
+    const int64_t want_lists = p->query_block * p->tail_parts;
+    p->tail_lists = want_lists < kTailLists ? want_lists : kTailLists;
+  }
 }
 
 tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, int32_t self,
@@ -242,12 +267,6 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
       }
     }
   }
-  // Grouped scan order: X against X through the register-list kernel with one
-  // reference split (each workgroup then scans the whole set from its own
-  // group on); by default from kOrderMinRows references on.
-  const bool want = o.reorder > 0 || (o.reorder == 0 && nr >= kOrderMinRows);
-  // (With runs, the tile scans the whole set in pieces whatever S is.)
-  p->order = (self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
   if (p->tile_kind == 1) {
     const int32_t r = (int32_t)kp / p->runs / 2;
     // (A box holds at least kUnitRows rows.)
@@ -256,20 +275,7 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
     p->tile_rows = 32 * mt::tile_waves(p->dpad_t, p->fold, r, true) *
                    mt::query_groups(p->dpad_t, p->fold, r);
   }
-  // Pruned scan: wherever the grouped order applies (its boxes cost 4 bytes
-  // a row and a stage test per 64 stages).
-  set_prune(p, !p->order ? kPruneNone : d > kBoxDim ? kPrunePivot : kPruneBox);
-  // Tail split of the register-list tile with one reference split (not with
-  // runs: their pieces already halve every workgroup's scan).
-  p->tail_parts = 1;
-  p->tail_auto = 0;
-  p->tail_lists = 0;
-  if (p->tile_kind == 1 && p->splits == 1 && p->runs == 1 && o.tail_parts != 1) {
-    p->tail_parts = o.tail_parts == 0 ? kMaxTailParts : o.tail_parts;
-    p->tail_auto = o.tail_parts == 0 ? 1 : 0;
-    const int64_t want_lists = p->query_block * p->tail_parts;
-    p->tail_lists = want_lists < kTailLists ? want_lists : kTailLists;
-  }
+  set_order_tail(p, o);
   return TOD_OK;
 }
 
@@ -352,6 +358,17 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   // The pruned scan's boxes go first: the same plan without them.
   if (p->prune) {
     Plan q = *p;
+    set_prune(&q, kPruneNone);
+    if (make_layout(q).total <= ws_bytes) {
+      *p = q;
+      return TOD_OK;
+    }
+  }
+  // A caller's query block stays; its lists may fit in fewer, longer splits.
+  if (o.query_block > 0 && o.ref_splits == 0) {
+    Plan q = *p;
+    set_splits(&q, long_splits(q.query_block, q.nr));
+    set_order_tail(&q, o);
     set_prune(&q, kPruneNone);
     if (make_layout(q).total <= ws_bytes) {
       *p = q;
@@ -454,7 +471,7 @@ tod_status make_plan_nwr(int64_t nq, int64_t nr, int64_t d, int32_t self, const 
   p->nr_pad = round_up(nr, 32);
   p->query_block = p->nq_pad;
   p->blocks = 1;
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits : nwr_splits(p->nq_pad, nr));
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits : long_splits(p->nq_pad, nr));
   p->waves_per_group = 4;
   p->tile_kind = 2;
   return TOD_OK;

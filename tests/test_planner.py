@@ -164,3 +164,28 @@ def test_workspace_sweep_monotone(tod, prec, mode, nq, nr):
         assert p["blocks"] == -(-nq // p["query_block"])
         assert p["query_block"] % 32 == 0 or p["blocks"] == 1
     assert accepted
+
+
+# A caller's query block in a workspace sized for splits of 2,048 references and
+# more (at most 16): accepted, whatever number of splits the planner prefers.
+@pytest.mark.parametrize("mode,nq,nr,d,qb", [
+    (0, 64, 50000, 32, 64), (0, 5000, 40000, 8, 256), (1, 30000, 30000, 20, 32),
+    (1, 30000, 30000, 20, 8192), (1, 100_000, 100_000, 6, 4096), (1, 100_000, 100_000, 32, 65536),
+])
+def test_fixed_block_takes_longer_splits(tod, mode, nq, nr, d, qb):
+    k = 10
+    splits = max(1, min(-(-2048 // -(-qb // 32)), nr // 2048, 16))
+    ws = tod.tod_workspace_size(nq, nr, d, k, mode,
+                                tod.options(query_block=qb, ref_splits=splits))
+    # (Without the pruned scan's boxes, which a plan gives up first.)
+    while True:
+        try:
+            tod.tod_plan_workspace(nq, nr, d, k, ws - 256, mode=mode,
+                                   opts=tod.options(query_block=qb, ref_splits=splits))
+            ws -= 256
+        except tod.TodError:
+            break
+    p = tod.tod_plan_workspace(nq, nr, d, k, ws, mode=mode, opts=tod.options(query_block=qb))
+    assert p["query_block"] == qb
+    with pytest.raises(tod.TodError):
+        tod.tod_plan_workspace(nq, nr, d, k, ws // 8, mode=mode, opts=tod.options(query_block=qb))
