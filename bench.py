@@ -483,6 +483,9 @@ def knn_roofline(wname, m):
     r["traffic"] = recorded_traffic(wname, kname)
     r["kernel"] = kname
     r["launch_ms"] = round(m["launch_ms"], 4)
+    # (The definition's work; the fraction of a scan that proves pairs irrelevant
+    # without evaluating them can exceed 1.)
+    r["pairs"] = "all n^2, also those the pruned scan rules out unevaluated"
     other = "alu" if m["bind"] == "mfma" else "mfma"
     r["other_view"] = m["views"][other]
     return r

@@ -42,10 +42,17 @@ constexpr int32_t kMaxKPrime = 256;
 // Tail split: at most 8 pieces, and a tail region of at most 2^18 lists.
 constexpr int32_t kMaxTailParts = 8;
 constexpr int64_t kTailLists = 1 << 18;
-// X against X from this many rows on runs as one split in the grouped order
-// with its pruned scan; below, splitting the references over more workgroups
-// gains more than the order costs (about 0.1 ms).
-constexpr int64_t kPruneMinRows = 20000;
+// X against X from this many rows on runs the pruned scan (one split in its
+// order).  Rows of more than 16 elements: below, more splits are the safer choice
+// (at 62,000 rows clustered ones take 0.51 to 0.68 of the two splits' time,
+// unclustered ones at most 1.04 of it; at 38,000 unclustered ones up to 1.56).
+// Shorter rows: boxes of columns rule less out the more columns there are, until
+// there are more of them.  At 75,000 to 95,000 rows of 4 to 6 columns the pruned
+// scan takes 0.43 to 0.97 of the plain one's time, of 8 up to 1.16, of 12 to 16 up
+// to 1.28 (270,000: 0.93 to 1.15); at 130,000 rows of 8 it takes 0.89 to 0.98.
+constexpr int64_t prune_rows(int64_t d) {
+  return d <= 6 ? 65536 : d <= 8 ? 1 << 17 : d <= tod::kBoxDim ? 1 << 20 : 60000;
+}
 // Smallest query block for which a shrunken plan reserves the pruned scan's boxes.
 constexpr int64_t kPruneMinBlock = 8192;
 
@@ -104,7 +111,10 @@ int64_t auto_splits(int64_t qb, int64_t nr, int64_t kp) {
   // (In workgroups of four waves.)
   const int64_t groups = (qb + 127) / 128, target = kp >= 64 ? 256 : 512;
   int64_t s = target / groups;
-  if (s < 2) s = (target + groups - 1) / groups;
+  // (Kernels with 16-entry lists hold more waves: few splits round up.  22,000 x
+  // 8 against itself took 0.82 of its speed in two splits instead of three; with
+  // 32 entries two are the faster ones, by a fifth.)
+  if (s < 2 || (kp <= 16 && s < 4)) s = (target + groups - 1) / groups;
   const int64_t cap = nr / (8 * kp) > 1 ? nr / (8 * kp) : 1;
   if (s > cap) s = cap;
   if (s > 64) s = 64;
@@ -139,6 +149,12 @@ static void set_prune(Plan* p, int32_t kind) {
                                   : order_groups(p->nr, p->d);
 }
 
+// The boxes a plan in the grouped order takes.
+static int32_t prune_kind(const Plan& p, const tod_options& o) {
+  if (o.reorder <= 0 && p.nr < prune_rows(p.d)) return kPruneNone;
+  return p.d > kBoxDim ? kPrunePivot : kPruneBox;
+}
+
 // What follows from the splits: the grouped order, the pruned scan, the tail split.
 static void set_order_tail(Plan* p, const tod_options& o) {
   // Grouped scan order: X against X through the register-list kernel with one
@@ -147,9 +163,7 @@ static void set_order_tail(Plan* p, const tod_options& o) {
   const bool want = o.reorder > 0 || (o.reorder == 0 && p->nr >= kOrderMinRows);
   // (With runs, the tile scans the whole set in pieces whatever S is.)
   p->order = (p->self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
-  // Pruned scan: wherever the grouped order applies (its boxes cost 4 bytes
-  // a row and a stage test per 64 stages).
-  set_prune(p, !p->order ? kPruneNone : p->d > kBoxDim ? kPrunePivot : kPruneBox);
+  set_prune(p, p->order ? prune_kind(*p, o) : kPruneNone);
   // Tail split of the register-list tile with one reference split (not with
   // runs: their pieces already halve every workgroup's scan).
   p->tail_parts = 1;
@@ -224,7 +238,7 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   // (The pruned scan of X against X cuts its own work: one split.)
   const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
                       prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
-                      (nr >= kPruneMinRows || o.reorder > 0);
+                      (nr >= prune_rows(d) || o.reorder > 0);
   set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr, kp));
   p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
@@ -399,11 +413,11 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   const size_t per = (size_t)q.kprime * sizeof(uint64_t);  // partial-list bytes per row and split
   const bool want = o.reorder > 0 || (o.reorder == 0 && q.nr >= kOrderMinRows);
   const bool may_order = q.self && q.tile_kind == 1 && want;
-  const int32_t prune = q.d > kBoxDim ? kPrunePivot : kPruneBox;
+  const int32_t prune = prune_kind(q, o);
   size_t need = 0;
   // (2: the order and the pruned scan, only while the block keeps
   // kPruneMinBlock rows; 1: the order alone; 0: neither.)
-  for (int with_order = may_order ? 2 : 0; with_order >= 0; --with_order) {
+  for (int with_order = !may_order ? 0 : prune ? 2 : 1; with_order >= 0; --with_order) {
     Plan f = q;
     f.query_block = 0;  // no partial lists: the fixed part of the layout
     f.order = with_order ? 1 : 0;
