@@ -15,8 +15,9 @@ SOURCES = ["api.hip", "prep.hip", "select.hip", "lof.hip", "tile_f32.hip", "tile
 # The fused tile kernels take maxima of MFMA accumulators (fmax, so that the
 # compiler sees the reads and inserts the wait states an MFMA result needs
 # before a VALU reads it).  Their operands are never NaN (prep rejects
-# non-finite input; masked entries are -inf), and -fno-honor-nans lets the
-# compiler form v_max3_f32 without quieting every operand first.
+# non-finite input; masked entries are -inf; the pruned scan's boxes are finite,
+# or -inf .. inf where they bound nothing), and -fno-honor-nans lets the compiler
+# form v_max3_f32 without quieting every operand first.
 NO_NAN_SOURCES = {"mtile_f16.hip", "mtile_bf16.hip", "tile_f32.hip", "tile_f16.hip",
                   "tile_bf16.hip"}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -105,6 +105,14 @@ assign_kernel(const float* __restrict__ x, int64_t n, int d, int32_t* __restrict
   lab[row] = best;
 }
 
+// An input element as the quantisation sees it: centred and scaled in fp64, |w| <
+// 2^E, then rounded to fp32 (by at most 2^(E-25)).  Differences of such values
+// neither overflow nor turn into NaN, whatever the magnitude of finite rows (the
+// scale alone can exceed fp32's range, and so can a difference of two rows).
+__device__ __forceinline__ float scaled_elem(float x, float mu, double s) {
+  return (float)(s * ((double)x - (double)mu));
+}
+
 // The pivots: kPivots of up to kSeedSamples evenly spaced rows (as many as fit
 // in LDS), the first one given, each next one drawn with probability
 // proportional to its squared distance from the nearest pivot so far
@@ -126,15 +134,16 @@ int seed_samples(int64_t n, int d) {
 
 __global__ void __launch_bounds__(kSeedThreads)
 pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
-                  const Ctrl* __restrict__ ctrl, int scale_exp, int32_t* __restrict__ srow) {
-  extern __shared__ float smp[];  // [m][d + 1], scaled
+                  const float* __restrict__ mu32, const Ctrl* __restrict__ ctrl, int scale_exp,
+                  int32_t* __restrict__ srow) {
+  extern __shared__ float smp[];  // [m][d + 1], centred and scaled
   __shared__ float wsum[kSeedThreads / 64];
   __shared__ int pick;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
+  const double sc = scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
   for (int e = tid; e < m * d; e += kSeedThreads) {
     const int i = e / d, t = e - i * d;
-    smp[i * (d + 1) + t] = x[((int64_t)i * n / m) * d + t] * sc;
+    smp[i * (d + 1) + t] = scaled_elem(x[((int64_t)i * n / m) * d + t], mu32[t], sc);
   }
   if (tid == 0) pick = m - 1;
   __syncthreads();
@@ -179,34 +188,34 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
 }
 
 // Longer rows with the pruned scan: groups by the nearest pivot.  Per row the
-// scaled distances s |x - seed_c| (s the quantisation's power of two, so that
-// they neither overflow nor underflow) go to pdist, and lab = 64 c + bin of
-// the nearest seed c, bin by half octaves of the squared distance: the rows of
-// a group are laid out by their distance from its seed, so that rows far from
-// every seed (outliers, clusters without a seed) do not widen the boxes of the
-// group's bulk.
+// distances to the pivots, in the quantisation's units (scaled_elem), go to
+// pdist, and lab = 64 c + bin of the nearest pivot c, bin by half octaves of the
+// squared distance: the rows of a group are laid out by their distance from its
+// pivot, so that rows far from every pivot (outliers, clusters without one) do
+// not widen the boxes of the group's bulk.
 __global__ void __launch_bounds__(kAssignThreads)
-assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d, const Ctrl* __restrict__ ctrl,
-                    int scale_exp, const int32_t* __restrict__ srow, float* __restrict__ pdist,
+assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d,
+                    const float* __restrict__ mu32, const Ctrl* __restrict__ ctrl, int scale_exp,
+                    const int32_t* __restrict__ srow, float* __restrict__ pdist,
                     int32_t* __restrict__ lab) {
-  extern __shared__ float seeds[];  // [kPivots][d]
+  extern __shared__ float seeds[];  // [kPivots][d], centred and scaled
+  const double sc = scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
   for (int i = threadIdx.x; i < kPivots * d; i += blockDim.x) {
     const int c = i / d, t = i - c * d;
-    seeds[i] = x[(int64_t)srow[c] * d + t];
+    seeds[i] = scaled_elem(x[(int64_t)srow[c] * d + t], mu32[t], sc);
   }
   __syncthreads();
   const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= n) return;
-  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
   float acc[kPivots];
 #pragma unroll
   for (int c = 0; c < kPivots; ++c) acc[c] = 0.0f;
   const float* in = x + row * d;
   for (int t = 0; t < d; ++t) {
-    const float v = in[t];
+    const float v = scaled_elem(in[t], mu32[t], sc);
 #pragma unroll
     for (int c = 0; c < kPivots; ++c) {
-      const float df = (v - seeds[c * d + t]) * sc;
+      const float df = v - seeds[c * d + t];
       acc[c] = fmaf(df, df, acc[c]);
     }
   }
@@ -217,7 +226,7 @@ assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d, const Ctrl* _
     best = acc[c] < bd ? c : best;
     bd = acc[c] < bd ? acc[c] : bd;
   }
-  // |s (x - seed)| < 2^(E+1) in every column: D^2 < 4 d 4^E.
+  // The difference is below 2^(E+1) in every column: D^2 < 4 d 4^E.
   const int top = (int)(__float_as_uint(ldexpf((float)d, 2 * scale_exp + 2)) >> 22);
   int bin = (int)(__float_as_uint(bd) >> 22) - top + (kRadBins - 1);
   bin = bin < 0 ? 0 : (bin > kRadBins - 1 ? kRadBins - 1 : bin);
@@ -380,7 +389,7 @@ kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __re
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t base = (int64_t)blockIdx.x * kKdChunk;
   const int rows = n - base < kKdChunk ? (int)(n - base) : kKdChunk;
-  const float sc = (float)scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
+  const double sc = scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
   constexpr int kPer = kKdChunk / kKdThreads;
   int32_t mine[kPer];
 #pragma unroll
@@ -389,7 +398,8 @@ kd_local_kernel(const float* __restrict__ x, int64_t n, int d, const float* __re
     mine[e] = i < rows ? perm[base + i] : 0;
     for (int t = 0; t < d; ++t)
       val[t * kKdChunk + i] =
-          i < rows ? (_Float16)((x[(int64_t)mine[e] * d + t] - mu32[t]) * sc) : (_Float16)0.0f;
+          i < rows ? (_Float16)scaled_elem(x[(int64_t)mine[e] * d + t], mu32[t], sc)
+                   : (_Float16)0.0f;
   }
   __syncthreads();
   if (wave < d) {
@@ -596,12 +606,14 @@ constexpr int kSubsPerBlock = 16;
 // Pivot boxes of the 32-row sub-tiles: one thread per (sub-tile, pivot).  The
 // quantised rows' distances differ from the rows' own by at most the two
 // radii (<= 2 P): every box is widened by P.  eps covers the fp32 rounding of
-// the distances; the absolute 2^-6 (rows reach 2^10 or more in these units)
-// covers differences below the smallest normal number.
+// the distances' arithmetic, `wide` that of the elements (scaled_elem: each row
+// of a pair is off by at most sqrt(d) 2^(E-25)) and differences below the
+// smallest normal number.  A box with a value that is not finite bounds nothing
+// (finite rows have none).
 __global__ void __launch_bounds__(kSubsPerBlock * kBoxDim)
 pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ perm,
                  const int32_t* __restrict__ lab, const int32_t* __restrict__ kstart, int64_t n,
-                 int64_t subs, float eps, const Ctrl* __restrict__ ctrl,
+                 int64_t subs, float eps, float wide, const Ctrl* __restrict__ ctrl,
                  float* __restrict__ box32, int32_t* __restrict__ substart) {
   const int t = threadIdx.x & (kBoxDim - 1);
   const int64_t sub = (int64_t)blockIdx.x * kSubsPerBlock + (threadIdx.x / kBoxDim);
@@ -609,16 +621,18 @@ pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ pe
   const int64_t r0 = 32 * sub;
   const int rows = n - r0 < 32 ? (int)(n - r0) : 32;
   float lo = INFINITY, hi = 0.0f;
+  bool bounded = true;
 #pragma unroll 8
   for (int i = 0; i < rows; ++i) {
     const float v = pdist[(int64_t)perm[r0 + i] * kPivots + t];
     lo = fminf(lo, v);
     hi = fmaxf(hi, v);
+    bounded = bounded && v < INFINITY;
   }
   const double pmax = __longlong_as_double((long long)ctrl->pmax_bits);
-  const float w = (float)(pmax * (1.0 + 0x1p-20)) + 0x1p-6f;
-  box32[sub * (2 * kBoxDim) + t] = lo * (1.0f - eps) - w;
-  box32[sub * (2 * kBoxDim) + kBoxDim + t] = hi * (1.0f + eps) + w;
+  const float w = (float)(pmax * (1.0 + 0x1p-20)) + wide;
+  box32[sub * (2 * kBoxDim) + t] = bounded ? lo * (1.0f - eps) - w : -INFINITY;
+  box32[sub * (2 * kBoxDim) + kBoxDim + t] = bounded ? hi * (1.0f + eps) + w : INFINITY;
   if (t == 0) substart[sub] = kstart[lab[perm[r0]]];
 }
 
@@ -943,10 +957,10 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
-                       m, tps, a.ctrl, p.scale_exp, srow);
+                       m, tps, a.mu32, a.ctrl, p.scale_exp, srow);
     hipLaunchKernelGGL(assign_pivot_kernel, dim3(ga), dim3(kAssignThreads),
-                       sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.ctrl,
-                       p.scale_exp, srow, a.pdist, a.lab);
+                       sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.mu32,
+                       a.ctrl, p.scale_exp, srow, a.pdist, a.lab);
   } else {
     if (G != kWideGroups) return hipErrorInvalidValue;
     hipLaunchKernelGGL(assign_kernel, dim3(ga), dim3(kAssignThreads),
@@ -995,8 +1009,9 @@ hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t st) {
   const dim3 bsub(kSubsPerBlock * kBoxDim);
   if (p.prune == kPrunePivot) {
     const float eps = (float)(p.d + 16) * 0x1p-24f;
+    const float wide = 0x1p-6f + ldexpf(sqrtf((float)p.d), p.scale_exp - 24);
     hipLaunchKernelGGL(pivot_box_kernel, dim3(gsub), bsub, 0, st, a.pdist, a.perm, a.lab, a.kstart,
-                       p.nr, subs, eps, a.ctrl, a.box32, a.substart);
+                       p.nr, subs, eps, wide, a.ctrl, a.box32, a.substart);
   } else if (p.precision == TOD_PREC_FP16) {
     hipLaunchKernelGGL(column_box_kernel<_Float16>, dim3(gsub), bsub, 0, st,
                        (const _Float16*)a.xq_r, p.nr, subs, (int)p.d, p.dpad, a.box32, a.substart);

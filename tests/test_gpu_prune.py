@@ -86,3 +86,42 @@ def test_pruned_equals_plain(env, kind, n, d, k, opt):
     rows = np.sort(rng.choice(n, 64, replace=False))
     oidx, odist = oracle.knn_self(x, k, rows=rows)
     compare_knn(x, x, rows, got[1].cpu().numpy()[rows], got[2].cpu().numpy()[rows], oidx, odist)
+
+
+def extreme(kind, rng):
+    n = 20000
+    if kind == "tiny":  # the quantisation's scale exceeds fp32's range; one constant column
+        x = 1e-36 * rng.standard_normal((n, 20))
+        x[:, 3] = 1e-36
+    elif kind == "tiny_binary":  # 0/1 features: rows agree with a pivot in many columns
+        x = 1e-36 * (rng.random((n, 40)) < 0.5)
+        x[:, 0] += 1e-39 * rng.standard_normal(n)
+    elif kind == "huge":  # rows of either sign in column 0 differ by more than FLT_MAX there
+        x = 1.6e38 * (2.0 * rng.random((n, 300)) - 1.0)
+        x[:, 0] = np.where(rng.random(n) < 0.5, 1.8e38, -1.8e38)
+    else:  # "offset": a common offset far above the spread
+        x = 1e6 + rng.standard_normal((n, 24))
+    return x.astype(np.float32)
+
+
+# Magnitudes at which fp32 cannot hold the quantisation's scale, or a difference of
+# two rows.  (20,000 rows: far more than the ones every query scans unconditionally.)
+@pytest.mark.parametrize("kind,k", [("tiny", 10), ("tiny_binary", 6), ("huge", 20), ("offset", 10)])
+def test_extreme_magnitudes(env, kind, k):
+    torch, tod, oracle = env
+    rng = np.random.default_rng(77)
+    x = extreme(kind, rng)
+    print("extreme", kind, flush=True)
+    xd = torch.from_numpy(x).cuda()
+    st = tod.new_stats()
+    got = tod.tod_knn_score(xd, k, tod.options(reorder=1), stats=st, return_lists=True)
+    assert st.reordered
+    ref = tod.tod_knn_score(xd, k, tod.options(reorder=-1), return_lists=True)
+    for u, v in zip(got, ref):
+        assert torch.equal(u, v)
+    rows = np.sort(rng.choice(len(x), 64, replace=False))
+    oidx, odist = oracle.knn_self(x, k, rows=rows)
+    if kind == "huge":  # (the distances themselves exceed fp32: the oracle's indices only)
+        assert np.array_equal(got[1].cpu().numpy()[rows], oidx)
+    else:
+        compare_knn(x, x, rows, got[1].cpu().numpy()[rows], got[2].cpu().numpy()[rows], oidx, odist)
