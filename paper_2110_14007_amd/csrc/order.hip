@@ -929,9 +929,7 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
     while ((1 << levels) < G) ++levels;
     const int m = kKdSamples << levels;
     const size_t lds = sizeof(uint64_t) * (size_t)m;
-    hipError_t e = hipFuncSetAttribute((const void*)kd_build_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    static_assert(sizeof(uint64_t) * kKdSamples * kOrdMaxC <= 65536, "no opt-in needed");
     hipLaunchKernelGGL(kd_build_kernel, dim3(1), dim3(kKdThreads), lds, st, a.xr, n, (int)p.d, m,
                        levels, reinterpret_cast<int2*>(a.oseed));
     hipLaunchKernelGGL(assign_kd_kernel, dim3(ga), dim3(kAssignThreads), 0, st, a.xr, n, (int)p.d,
@@ -953,8 +951,11 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
     int tps = 2;  // threads per sample
     while (m * tps * 2 <= kSeedThreads && tps < 64) tps *= 2;
     const size_t lds = sizeof(float) * (size_t)m * (size_t)(p.d + 1);
+    // (The attribute is the function's, not the call's: its bound, whatever this
+    // call needs, so that calls of other threads stay within it.)
     hipError_t e = hipFuncSetAttribute((const void*)pivot_seed_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(sizeof(float) * kSeedFloats));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
                        m, tps, a.mu32, a.ctrl, p.scale_exp, srow);
@@ -982,8 +983,10 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
     const int chunk = kd_chunk(n);
     const size_t lds = (size_t)chunk * (sizeof(uint32_t) + sizeof(_Float16) * (p.d < 2 ? 2 : p.d));
     const auto kern = chunk == kKdChunkMost ? kd_local_kernel<kKdChunkMost> : kd_local_kernel<1024>;
+    // (The most any row length takes, as above.)
+    const size_t most = (size_t)chunk * (sizeof(uint32_t) + sizeof(_Float16) * kBoxDim);
     hipError_t e = hipFuncSetAttribute((const void*)kern,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)((n + chunk - 1) / chunk)),
                        dim3(kKdThreads), lds, st, a.xr, n, (int)p.d, a.mu32, a.ctrl, p.scale_exp,

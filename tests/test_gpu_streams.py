@@ -64,3 +64,37 @@ def test_two_threads_two_streams():
     for got in results["lof"]:
         np.testing.assert_array_equal(got[0], ref2[0])
         np.testing.assert_array_equal(got[1], ref2[1])
+
+
+def test_two_threads_different_lds():
+    # The pruned scan's preparation takes LDS by the row length.  Two threads whose
+    # calls need 43 KB and 147 KB of it for the same kernel, many times over.
+    import torch
+    from paper_2110_14007_amd import tod
+
+    rng = np.random.default_rng(3)
+    xs = [torch.from_numpy(rng.standard_normal((3000, d)).astype(np.float32)).cuda()
+          for d in (20, 100)]
+    opt = dict(reorder=1, ref_splits=1)
+    refs = [tod.tod_knn_score(x, 5, tod.options(**opt), return_lists=True) for x in xs]
+    torch.cuda.synchronize()
+    errors = []
+
+    def worker(x, ref):
+        try:
+            s, ws = torch.cuda.Stream(), tod.Workspace()
+            for i in range(200):
+                got = tod.tod_knn_score(x, 5, tod.options(**opt), ws, stream=s, return_lists=True)
+                s.synchronize()
+                if not all(torch.equal(a, b) for a, b in zip(got, ref)):
+                    raise AssertionError("call %d differs" % i)
+        except Exception as e:  # reported below, after both threads end
+            errors.append(repr(e))
+
+    threads = [threading.Thread(target=worker, args=a) for a in zip(xs, refs)]
+    say("two threads, two row lengths")
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
