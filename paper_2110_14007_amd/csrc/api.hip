@@ -53,8 +53,6 @@ constexpr int64_t kTailLists = 1 << 18;
 constexpr int64_t prune_rows(int64_t d) {
   return d <= 6 ? 65536 : d <= 8 ? 1 << 17 : d <= tod::kBoxDim ? 1 << 20 : 60000;
 }
-// Smallest query block for which a shrunken plan reserves the pruned scan's boxes.
-constexpr int64_t kPruneMinBlock = 8192;
 
 tod_status resolve_options(const tod_options* in, tod_options* out) {
   tod_default_options(out);
@@ -378,15 +376,19 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
       return TOD_OK;
     }
   }
-  // A caller's query block stays; its lists may fit in fewer, longer splits.
-  if (o.query_block > 0 && o.ref_splits == 0) {
-    Plan q = *p;
-    set_splits(&q, long_splits(q.query_block, q.nr));
-    set_order_tail(&q, o);
-    set_prune(&q, kPruneNone);
-    if (make_layout(q).total <= ws_bytes) {
-      *p = q;
-      return TOD_OK;
+  // The same block in fewer, longer splits, down to one (in the grouped order).
+  if (o.ref_splits == 0) {
+    const int64_t most = auto_splits(p->query_block, p->nr, p->kprime);
+    const int64_t wide = long_splits(p->query_block, p->nr);
+    for (int64_t s = most > wide ? most : wide; s >= 1; --s) {
+      Plan q = *p;
+      set_splits(&q, s);
+      set_order_tail(&q, o);
+      set_prune(&q, kPruneNone);
+      if (make_layout(q).total <= ws_bytes) {
+        *p = q;
+        return TOD_OK;
+      }
     }
   }
   if (o.query_block > 0 || o.ref_splits > 0) {
@@ -405,43 +407,53 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
       return TOD_OK;
     }
   }
-  // The grouped scan order needs buffers of its own and applies only with one
-  // split; a shrunken plan may end up with one split where the one-block plan
-  // had several.  The order's buffers are therefore reserved first (where the
-  // order could apply), and left out only when the block does not fit beside
-  // them: the order is an optimisation, the block is not.
-  const size_t per = (size_t)q.kprime * sizeof(uint64_t);  // partial-list bytes per row and split
+  // Smaller blocks.  The grouped scan order needs buffers of its own and applies
+  // only with one split; a shrunken plan may end up with one split where the
+  // one-block plan had several.  The order's buffers are therefore reserved first
+  // (where the order could apply), and left out only when the block does not fit
+  // beside them: the order is an optimisation, the block is not.
   const bool want = o.reorder > 0 || (o.reorder == 0 && q.nr >= kOrderMinRows);
   const bool may_order = q.self && q.tile_kind == 1 && want;
   const int32_t prune = prune_kind(q, o);
+  // The layout in blocks of qb rows and s splits.
+  const auto shape = [](Plan* f, int64_t qb, int64_t s) {
+    f->query_block = qb;
+    f->blocks = (f->nq + qb - 1) / qb;
+    set_splits(f, s);
+    return make_layout(*f).total;
+  };
   size_t need = 0;
-  // (2: the order and the pruned scan, only while the block keeps
-  // kPruneMinBlock rows; 1: the order alone; 0: neither.)
+  // The rows of the largest block that fits with one split, 0 if none does.  (By
+  // the layout itself: the pivot distances lie over the lists, so that a sum of
+  // the parts would count them twice.)
+  const auto largest = [&](Plan* f) -> int64_t {
+    int64_t lo = 0, hi = f->nq_pad / 32;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi + 1) / 2;
+      if (shape(f, 32 * mid, 1) <= ws_bytes) lo = mid;
+      else hi = mid - 1;
+    }
+    return 32 * lo;
+  };
+  // (2: the order and the pruned scan, only while the block keeps one split of
+  // its own accord and the boxes leave it half the rows it has without them: rows
+  // that the boxes cannot tell apart lose by the part rounds of more blocks;
+  // 1: the order alone; 0: neither.)
   for (int with_order = !may_order ? 0 : prune ? 2 : 1; with_order >= 0; --with_order) {
     Plan f = q;
-    f.query_block = 0;  // no partial lists: the fixed part of the layout
     f.order = with_order ? 1 : 0;
     set_prune(&f, with_order == 2 ? prune : kPruneNone);
-    const size_t fixed = make_layout(f).total;
-    need = fixed + 32 * per + 256;
-    if (ws_bytes < need) continue;
-    const size_t room = ws_bytes - fixed - 256;  // the partial region's alignment slack
-    int64_t qb = (int64_t)(room / per) / 32 * 32;
-    if (qb > f.nq_pad) qb = f.nq_pad;
-    if (with_order == 2) {
-      // (The plan's per-tile words come off the room; one split.)
-      qb = (int64_t)(room / (per + 1)) / 32 * 32;
-      if (qb > f.nq_pad) qb = f.nq_pad;
-      if (qb < kPruneMinBlock && qb < f.nq_pad) continue;
-      f.query_block = qb;
-      if (auto_splits(qb, f.nr, f.kprime) != 1 || make_layout(f).total > ws_bytes) continue;
-    }
+    need = shape(&f, 32, 1);
+    const int64_t qb = largest(&f);
+    if (qb == 0) continue;
     int64_t s = auto_splits(qb, f.nr, f.kprime);
-    const int64_t smax = (int64_t)(room / ((size_t)qb * per));
-    if (s > smax) s = smax;
-    f.query_block = qb;
-    f.blocks = (f.nq + qb - 1) / qb;
-    set_splits(&f, s);
+    if (with_order == 2) {
+      Plan g = f;
+      set_prune(&g, kPruneNone);
+      if (s != 1 || 2 * qb < largest(&g)) continue;
+    }
+    while (s > 1 && shape(&f, qb, s) > ws_bytes) --s;
+    (void)shape(&f, qb, s);
     f.order = (with_order && (f.splits == 1 || f.runs > 1)) ? 1 : 0;
     if (!f.order) set_prune(&f, kPruneNone);
     if (make_layout(f).total > ws_bytes) {

@@ -189,3 +189,30 @@ def test_fixed_block_takes_longer_splits(tod, mode, nq, nr, d, qb):
     assert p["query_block"] == qb
     with pytest.raises(tod.TodError):
         tod.tod_plan_workspace(nq, nr, d, k, ws // 8, mode=mode, opts=tod.options(query_block=qb))
+
+
+# A workspace that holds the whole query set in few splits stays one block, also
+# where the planner prefers more splits than fit, down to the last byte.
+@pytest.mark.parametrize("mode,nq,nr,d,k,prec", [
+    (0, 7, 2816, 28, 100, "auto"), (0, 5, 455, 6, 5, "fp32"), (0, 2, 2232, 522, 1, "fp32"),
+    (1, 2552, 2552, 48, 64, "auto"), (0, 30173, 4084, 53, 1, "fp32"), (0, 42, 308, 35, 1, "fp32"),
+    (1, 30000, 30000, 20, 10, "auto"), (0, 64, 50000, 32, 10, "auto"),
+])
+def test_one_block_in_few_splits(tod, mode, nq, nr, d, k, prec):
+    for splits in {1, max(1, min(-(-2048 // -(-nq // 32)), nr // 2048, 16))}:
+        ws = tod.tod_workspace_size(nq, nr, d, k, mode, tod.options(precision=prec,
+                                                                    ref_splits=splits))
+        p = tod.tod_plan_workspace(nq, nr, d, k, ws, mode=mode, opts=tod.options(precision=prec))
+        assert p["blocks"] == 1
+
+
+# The pivot distances lie over the partial lists: a block shrunk to the workspace
+# counts them once.
+@pytest.mark.parametrize("n,d,k,share", [(2797960, 98, 1, 0.95), (2797960, 98, 1, 0.9),
+                                         (2797960, 98, 1, 0.8), (1500000, 40, 5, 0.85)])
+def test_shrunken_block_uses_its_room(tod, n, d, k, share):
+    plain = tod.tod_workspace_size(n, n, d, k, 1, tod.options(reorder=-1, ref_splits=1))
+    ws = int(share * plain)
+    p = tod.tod_plan_workspace(n, n, d, k, ws, mode=1)
+    q = tod.tod_plan_workspace(n, n, d, k, ws, mode=1, opts=tod.options(reorder=-1))
+    assert p["query_block"] >= 0.5 * q["query_block"]
