@@ -42,6 +42,8 @@ constexpr int32_t kMaxKPrime = 256;
 // Tail split: at most 8 pieces, and a tail region of at most 2^18 lists.
 constexpr int32_t kMaxTailParts = 8;
 constexpr int64_t kTailLists = 1 << 18;
+// Smallest query block of a pruned scan whose tiles cannot be cut (prune_block).
+constexpr int64_t kUncutRows = 1 << 17;
 // X against X from this many rows on runs the pruned scan (one split in its
 // order).  Rows of more than 16 elements: below, more splits are the safer choice
 // (at 62,000 rows clustered ones take 0.51 to 0.68 of the two splits' time,
@@ -153,6 +155,15 @@ static int32_t prune_kind(const Plan& p, const tod_options& o) {
   return p.d > kBoxDim ? kPrunePivot : kPruneBox;
 }
 
+// Whether a block is one for the pruned scan.  Without a region for the lists of cut
+// scans (tail_parts = 1, or a small workspace) it takes two rounds of workgroups and
+// more: the order gathers outliers, which scan everything, into tiles of their own,
+// and those bound a shorter launch (10^5 clustered rows of 32 in one block: 3.3 ms
+// uncut, 2.5 in the plain scan; 150,000: 3.7 and 4.1).
+static bool prune_block(const Plan& p) {
+  return p.runs > 1 || p.tail_lists > 0 || p.query_block >= kUncutRows;
+}
+
 // What follows from the splits: the grouped order, the pruned scan, the tail split.
 static void set_order_tail(Plan* p, const tod_options& o) {
   // Grouped scan order: X against X through the register-list kernel with one
@@ -161,7 +172,6 @@ static void set_order_tail(Plan* p, const tod_options& o) {
   const bool want = o.reorder > 0 || (o.reorder == 0 && p->nr >= kOrderMinRows);
   // (With runs, the tile scans the whole set in pieces whatever S is.)
   p->order = (p->self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
-  set_prune(p, p->order ? prune_kind(*p, o) : kPruneNone);
   // Tail split of the register-list tile with one reference split (not with
   // runs: their pieces already halve every workgroup's scan).
   p->tail_parts = 1;
@@ -173,6 +183,7 @@ static void set_order_tail(Plan* p, const tod_options& o) {
     const int64_t want_lists = p->query_block * p->tail_parts;
     p->tail_lists = want_lists < kTailLists ? want_lists : kTailLists;
   }
+  set_prune(p, p->order ? prune_kind(*p, o) : kPruneNone);
 }
 
 tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, int32_t self,
@@ -400,7 +411,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   q.tail_parts = 1;
   q.tail_auto = 0;
   q.tail_lists = 0;
-  for (int with_prune = q.prune ? 1 : 0; with_prune >= 0; --with_prune) {
+  for (int with_prune = q.prune && prune_block(q) ? 1 : 0; with_prune >= 0; --with_prune) {
     if (!with_prune) set_prune(&q, kPruneNone);
     if (make_layout(q).total <= ws_bytes) {
       *p = q;
@@ -414,7 +425,6 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   // beside them: the order is an optimisation, the block is not.
   const bool want = o.reorder > 0 || (o.reorder == 0 && q.nr >= kOrderMinRows);
   const bool may_order = q.self && q.tile_kind == 1 && want;
-  const int32_t prune = prune_kind(q, o);
   // The layout in blocks of qb rows and s splits.
   const auto shape = [](Plan* f, int64_t qb, int64_t s) {
     f->query_block = qb;
@@ -439,10 +449,11 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   // its own accord and the boxes leave it half the rows it has without them: rows
   // that the boxes cannot tell apart lose by the part rounds of more blocks;
   // 1: the order alone; 0: neither.)
-  for (int with_order = !may_order ? 0 : prune ? 2 : 1; with_order >= 0; --with_order) {
+  for (int with_order = may_order ? 2 : 0; with_order >= 0; --with_order) {
     Plan f = q;
     f.order = with_order ? 1 : 0;
-    set_prune(&f, with_order == 2 ? prune : kPruneNone);
+    set_prune(&f, with_order == 2 ? prune_kind(q, o) : kPruneNone);
+    if (with_order == 2 && !f.prune) continue;
     need = shape(&f, 32, 1);
     const int64_t qb = largest(&f);
     if (qb == 0) continue;
@@ -450,7 +461,8 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
     if (with_order == 2) {
       Plan g = f;
       set_prune(&g, kPruneNone);
-      if (s != 1 || 2 * qb < largest(&g)) continue;
+      (void)shape(&f, qb, 1);
+      if (s != 1 || !prune_block(f) || 2 * qb < largest(&g)) continue;
     }
     while (s > 1 && shape(&f, qb, s) > ws_bytes) --s;
     (void)shape(&f, qb, s);
@@ -611,6 +623,10 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
                           "; the one-block plan needs " + std::to_string(L.total) + ")");
     L = tod::make_layout(p);
   }
+  if (p.prune && !tod::prune_block(p)) {  // (the boxes' room stays unused)
+    tod::set_prune(&p, tod::kPruneNone);
+    L = tod::make_layout(p);
+  }
   char* base = (char*)ws;
   Args a;
   memset(&a, 0, sizeof(a));
@@ -669,8 +685,9 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
     a.sbox = (float*)(base + L.sbox);
     a.xbox = (float*)(base + L.xbox);
     a.substart = (int32_t*)(base + L.substart);
-    // The work plan: one run, one split, pieces chosen by the planner.
-    if (p.runs == 1 && p.splits == 1 && p.tail_auto && tod::plan_extra(p) > 0) {
+    // The work plan (without a tail region it cuts no scan, but still orders the
+    // tiles and decides between the two scans).  Two runs have pieces of their own.
+    if (p.runs == 1) {
       a.plan = (int32_t*)(base + L.plan);
       a.plan_cap = tod::plan_extra(p);
       a.plan_tiles = 1 + 2 * a.plan_cap;

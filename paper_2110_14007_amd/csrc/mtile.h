@@ -420,7 +420,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   const bool active = group * 32 * NQ < q_rows;  // uniform per wave
   const int64_t q0 = q_begin + group * 32 * NQ;
   const int split = piece;  // reference split (no pieces)
-  const bool pieces = parts > 1 || (PR && a.plan);
+  const bool pieces = parts > 1 || PR;
   const int64_t r_begin = pieces ? 0 : (int64_t)split * a.split_len;
   const int64_t r_end = r_begin + a.split_len < a.nr ? r_begin + a.split_len : a.nr;
   const int64_t r_end32 = (r_end + 31) & ~(int64_t)31;  // rows < r_end32 exist (padded copy)

@@ -2,6 +2,7 @@
 queries than their K'-th neighbours are skipped.  Every output must equal the
 plain order's (reorder = -1) bit for bit, and sampled rows the oracle's.
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -66,6 +67,9 @@ def data(kind, n, d, rng):
     ("two", 21000, 1, 3, {}),
     ("two", 21000, 5, 20, {}),
     ("clusters", 70, 5, 4, {"ref_splits": 1}),
+    # scans that may not be cut, and ones cut in a region of another size
+    ("clusters", 131105, 20, 10, {"tail_parts": 1}),
+    ("clusters", 20011, 40, 10, {"tail_parts": 8, "ref_splits": 1, "query_block": 4096}),
 ])
 def test_pruned_equals_plain(env, kind, n, d, k, opt):
     torch, tod, oracle = env
@@ -125,3 +129,29 @@ def test_extreme_magnitudes(env, kind, k):
         assert np.array_equal(got[1].cpu().numpy()[rows], oidx)
     else:
         compare_knn(x, x, rows, got[1].cpu().numpy()[rows], got[2].cpu().numpy()[rows], oidx, odist)
+
+
+# A workspace without room for the tail region: the pruned scan's tiles stay uncut.
+@pytest.mark.parametrize("kind,share", [("clusters", 0.9), ("uniform", 0.9), ("clusters", 0.6)])
+def test_pruned_in_small_workspace(env, kind, share):
+    torch, tod, oracle = env
+    n, d, k = 150000, 24, 10
+    x = data(kind, n, d, np.random.default_rng(9))
+    print("pruned, small workspace", kind, share, flush=True)
+    xd = torch.from_numpy(x).cuda()
+    full = tod.tod_workspace_size(n, n, d, k, 0, tod.options(exclude_self=True, tail_parts=1))
+    ws = torch.empty(int(share * full) + 256, dtype=torch.uint8, device="cuda")
+    at = -ws.data_ptr() % 256
+    lib = tod.raw_library()
+    score = torch.empty(n, device="cuda")
+    idx = torch.empty((n, k), dtype=torch.int64, device="cuda")
+    dist = torch.empty((n, k), device="cuda")
+    o, st = tod.options(), tod.new_stats()
+    rc = lib.tod_knn_score(xd.data_ptr(), n, d, k, ctypes.byref(o), ws.data_ptr() + at,
+                           int(share * full), torch.cuda.current_stream().cuda_stream,
+                           score.data_ptr(), idx.data_ptr(), dist.data_ptr(), ctypes.byref(st))
+    assert rc == 0, tod.last_error()
+    assert st.tail_parts == 1 and st.reordered
+    ref = tod.tod_knn_score(xd, k, tod.options(reorder=-1), return_lists=True)
+    for u, v in zip((score, idx, dist), ref):
+        assert torch.equal(u, v)
