@@ -120,48 +120,92 @@ __device__ __forceinline__ float scaled_elem(float x, float mu, double s) {
 // numbers).  Rows at random would leave some of ten clusters without a pivot in
 // four runs of five, and stages of two such clusters can hardly be told apart:
 // at 10^6 rows of 64 the tile took 65 to 85 ms from seed to seed, against 47.
-// One workgroup, bound by the latency of its kPivots dependent rounds: the
-// samples sit in LDS (read from global memory in every round it took 80 us).
+// One workgroup, bound by its kPivots dependent rounds over the samples in LDS
+// (16-byte reads: 59 us at 75,000 rows of 128, 84 with 4-byte ones; 37 at rows
+// of 32).
+//
+// Rows that the pivots cannot tell apart are recognised here, before the rest of
+// the preparation is paid: of the pairs of up to kFlatQueries samples (no pivots
+// themselves) with all samples, the share that no pivot's distances separate by
+// more than twice the first one's distance to its nearest pivot, the plan's
+// estimate of a neighbour's distance.  Boxes hold whole stages, so they rule out
+// no more than that: on Gaussian and uniform rows of 17 to 256 elements the share
+// was 0.85 and more (boxes: 0.998 and more), on ten or five clusters 0.09 to 0.22
+// (0.14 to 0.38), on a curved sheet 0.16 to 0.22 (0.45 to 0.54).  From kFlatShare
+// on the call keeps to evenly spaced seeds, input order within their groups and
+// the plain scan: pivots and distance bins made that 3 to 15 % slower there (their
+// order puts the outliers into tiles of their own, and a group's rows in the order
+// of their distance, not at random, fill the lists more often).
+constexpr int kFlatQueries = 32;
+constexpr float kFlatShare = 0.75f;
 constexpr int kSeedSamples = 512;
 constexpr int kSeedThreads = 1024;
 constexpr int kSeedFloats = 36 * 1024;  // LDS for the samples
 
+// Floats from one sample to the next: whole 16-byte chunks, zero-padded, and one
+// more to spread the samples over the banks.
+__host__ __device__ constexpr int seed_stride(int d) { return (d + 3) / 4 * 4 + 4; }
+
 int seed_samples(int64_t n, int d) {
-  int64_t m = kSeedFloats / (d + 1);
+  int64_t m = kSeedFloats / seed_stride(d);
   m = m < kSeedSamples ? m : kSeedSamples;
   return (int)(m < n ? m : n);
 }
 
 __global__ void __launch_bounds__(kSeedThreads)
 pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
-                  const float* __restrict__ mu32, const Ctrl* __restrict__ ctrl, int scale_exp,
-                  int32_t* __restrict__ srow) {
-  extern __shared__ float smp[];  // [m][d + 1], centred and scaled
+                  const float* __restrict__ mu32, Ctrl* __restrict__ ctrl, int scale_exp,
+                  int may_flat, float* __restrict__ dist, int32_t* __restrict__ srow) {
+  extern __shared__ __align__(16) float smp[];  // [m][stride], centred and scaled
   __shared__ float wsum[kSeedThreads / 64];
-  __shared__ int pick;
+  __shared__ int32_t rows[kSeedSamples], piv[kPivots];
+  __shared__ int pick, cnt[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double sc = scale_from_maxabs(ctrl->maxabs_bits, scale_exp);
-  for (int e = tid; e < m * d; e += kSeedThreads) {
-    const int i = e / d, t = e - i * d;
-    smp[i * (d + 1) + t] = scaled_elem(x[((int64_t)i * n / m) * d + t], mu32[t], sc);
+  // (One 64-bit division per sample, and eight elements' loads at once.)
+  if (tid < m) rows[tid] = (int32_t)((int64_t)tid * n / m);
+  __syncthreads();
+  const int stride = seed_stride(d), dp = stride - 4;
+  constexpr int kLoads = 8;
+  for (int e0 = tid; e0 < m * dp; e0 += kLoads * kSeedThreads) {
+    float v[kLoads], mu[kLoads];
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int e = e0 + u * kSeedThreads < m * dp ? e0 + u * kSeedThreads : e0;
+      const int i = e / dp, t = e - i * dp < d ? e - i * dp : d - 1;
+      v[u] = x[(int64_t)rows[i] * d + t];
+      mu[u] = mu32[t];
+    }
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int e = e0 + u * kSeedThreads;
+      const int i = e / dp, t = e - i * dp;
+      if (i < m) smp[i * stride + t] = t < d ? scaled_elem(v[u], mu[u], sc) : 0.0f;
+    }
   }
-  if (tid == 0) pick = m - 1;
+  if (tid == 0) {
+    pick = m - 1;
+    cnt[0] = cnt[1] = 0;
+  }
   __syncthreads();
   const int i = tid / tps, sub = tid & (tps - 1);  // sample, one of its tps threads
-  const float* in = smp + (i < m ? i : 0) * (d + 1);
+  const float4* const smp4 = reinterpret_cast<const float4*>(smp);
+  const float4* in = smp4 + (i < m ? i : 0) * (stride / 4);
   float near = INFINITY;
   int p = 0;
   for (int c = 0; c < kPivots; ++c) {
-    if (tid == 0) srow[c] = (int32_t)((int64_t)p * n / m);
-    const float* pv = smp + p * (d + 1);
+    if (tid == 0) piv[c] = rows[p];
+    const float4* pv = smp4 + p * (stride / 4);
     float acc = 0.0f;
-#pragma unroll 8
-    for (int t = sub; t < d; t += tps) {
-      const float df = in[t] - pv[t];
-      acc = fmaf(df, df, acc);
+#pragma unroll 4
+    for (int t = sub; t < dp / 4; t += tps) {
+      const float4 a = in[t], b = pv[t];
+      const float d0 = a.x - b.x, d1 = a.y - b.y, d2 = a.z - b.z, d3 = a.w - b.w;
+      acc = fmaf(d0, d0, fmaf(d1, d1, fmaf(d2, d2, fmaf(d3, d3, acc))));
     }
     for (int off = 1; off < tps; off <<= 1) acc += __shfl_xor(acc, off, 64);
     near = fminf(near, acc);
+    if (may_flat && i < m && sub == 0) dist[(int64_t)i * kPivots + c] = sqrtf(acc);
     // Inclusive sums of the weights in sample order.
     float incl = i < m && sub == 0 ? near : 0.0f;
     for (int off = 1; off < 64; off <<= 1) {
@@ -185,6 +229,49 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
     __syncthreads();  // every thread has read pick before it is reset
     if (tid == 0) pick = m - 1;
   }
+  if (!may_flat) {  // uniform
+    if (tid < kPivots) srow[tid] = piv[tid];
+    return;
+  }
+  // The samples' distances (each thread reads what it wrote) take the samples'
+  // place in LDS: [m][kPivots], then each sample's distance to its nearest pivot.
+  float* const near_of = smp + m * kPivots;
+  if (i < m && sub == 0) {
+    for (int c = 0; c < kPivots; ++c) smp[i * kPivots + c] = dist[(int64_t)i * kPivots + c];
+    near_of[i] = sqrtf(near);
+  }
+  __syncthreads();
+  const int j = tid % m, nq = m < kFlatQueries ? m : kFlatQueries;
+  float dj[kPivots];
+#pragma unroll
+  for (int c = 0; c < kPivots; ++c) dj[c] = smp[j * kPivots + c];
+  int seen = 0, live = 0;
+  for (int q = tid / m; tid < kSeedThreads / m * m && q < nq; q += kSeedThreads / m) {
+    const int s = q * m / nq;
+    float lb = 0.0f;
+#pragma unroll
+    for (int c = 0; c < kPivots; c += 4) {
+      const float4 dq = smp4[(s * kPivots + c) / 4];
+      lb = fmaxf(fmaxf(lb, fabsf(dq.x - dj[c])), fabsf(dq.y - dj[c + 1]));
+      lb = fmaxf(fmaxf(lb, fabsf(dq.z - dj[c + 2])), fabsf(dq.w - dj[c + 3]));
+    }
+    if (near_of[s] > 0.0f) {
+      ++seen;
+      live += lb > 2.0f * near_of[s] ? 0 : 1;
+    }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    seen += __shfl_xor(seen, off, 64);
+    live += __shfl_xor(live, off, 64);
+  }
+  if (lane == 0) {
+    atomicAdd(&cnt[0], seen);
+    atomicAdd(&cnt[1], live);
+  }
+  __syncthreads();
+  const bool flat = cnt[0] > 0 && (float)cnt[1] >= kFlatShare * (float)cnt[0];
+  if (tid < kPivots) srow[tid] = flat ? (int32_t)((int64_t)tid * n / kPivots) : piv[tid];
+  if (tid == 0) ctrl->flat = flat ? 1u : 0u;
 }
 
 // Longer rows with the pruned scan: groups by the nearest pivot.  Per row the
@@ -192,7 +279,8 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
 // pdist, and lab = 64 c + bin of the nearest pivot c, bin by half octaves of the
 // squared distance: the rows of a group are laid out by their distance from its
 // pivot, so that rows far from every pivot (outliers, clusters without one) do
-// not widen the boxes of the group's bulk.
+// not widen the boxes of the group's bulk.  Rows the pivots cannot tell apart
+// (ctrl->flat): srow holds evenly spaced rows, and a group is one bin.
 __global__ void __launch_bounds__(kAssignThreads)
 assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d,
                     const float* __restrict__ mu32, const Ctrl* __restrict__ ctrl, int scale_exp,
@@ -230,7 +318,9 @@ assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d,
   const int top = (int)(__float_as_uint(ldexpf((float)d, 2 * scale_exp + 2)) >> 22);
   int bin = (int)(__float_as_uint(bd) >> 22) - top + (kRadBins - 1);
   bin = bin < 0 ? 0 : (bin > kRadBins - 1 ? kRadBins - 1 : bin);
-  lab[row] = best * kRadBins + bin;
+  const bool flat = ctrl->flat != 0;
+  lab[row] = best * kRadBins + (flat ? 0 : bin);
+  if (flat) return;
   float4* out = reinterpret_cast<float4*>(pdist + row * kPivots);
 #pragma unroll
   for (int c = 0; c < kPivots / 4; ++c)
@@ -619,6 +709,8 @@ pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ pe
   const int64_t sub = (int64_t)blockIdx.x * kSubsPerBlock + (threadIdx.x / kBoxDim);
   if (sub >= subs) return;
   const int64_t r0 = 32 * sub;
+  if (t == 0) substart[sub] = kstart[lab[perm[r0]]];
+  if (ctrl->flat) return;  // (no distances; no box is read)
   const int rows = n - r0 < 32 ? (int)(n - r0) : 32;
   float lo = INFINITY, hi = 0.0f;
   bool bounded = true;
@@ -633,7 +725,6 @@ pivot_box_kernel(const float* __restrict__ pdist, const int32_t* __restrict__ pe
   const float w = (float)(pmax * (1.0 + 0x1p-20)) + wide;
   box32[sub * (2 * kBoxDim) + t] = bounded ? lo * (1.0f - eps) - w : -INFINITY;
   box32[sub * (2 * kBoxDim) + kBoxDim + t] = bounded ? hi * (1.0f + eps) + w : INFINITY;
-  if (t == 0) substart[sub] = kstart[lab[perm[r0]]];
 }
 
 // Boxes of the quantised columns of the 32-row sub-tiles (exact values).
@@ -665,13 +756,15 @@ column_box_kernel(const T* __restrict__ xq, int64_t n, int64_t subs, int d, int 
 // of chunks of stages from those of the stages.
 __global__ void __launch_bounds__(256)
 stage_box_kernel(const float* __restrict__ box32, int64_t subs, int64_t stages, int nsub,
-                 float* __restrict__ sbox) {
+                 const Ctrl* __restrict__ ctrl, float* __restrict__ sbox) {
+  if (ctrl->flat) return;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t st = i / (2 * kBoxDim);
   const int t = (int)(i % (2 * kBoxDim));
   if (st >= stages) return;
   const int64_t s0 = st * nsub, s1 = s0 + nsub < subs ? s0 + nsub : subs;
   float v = box32[s0 * (2 * kBoxDim) + t];
+#pragma unroll 8
   for (int64_t s = s0 + 1; s < s1; ++s) {
     const float o = box32[s * (2 * kBoxDim) + t];
     v = t < kBoxDim ? fminf(v, o) : fmaxf(v, o);
@@ -691,7 +784,9 @@ constexpr int kPlanSamples = 2048;
 __global__ void __launch_bounds__(256)
 plan_estimate_kernel(const float* __restrict__ box32, const float* __restrict__ sbox,
                      int64_t stages, int64_t sub0, int64_t nsubs, int subs_per_tile,
-                     int64_t tiles, int prune, int32_t* __restrict__ rec) {
+                     int64_t tiles, int prune, const Ctrl* __restrict__ ctrl,
+                     int32_t* __restrict__ rec) {
+  if (ctrl->flat) return;
   const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   if (t >= tiles) return;  // uniform per wave
@@ -784,7 +879,11 @@ constexpr float kPieceCharge = 0.25f;
 
 __global__ void __launch_bounds__(kPlanThreads)
 plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, float l0, float fixed,
-                   int32_t* __restrict__ plan, int64_t rec_at) {
+                   const Ctrl* __restrict__ ctrl, int32_t* __restrict__ plan, int64_t rec_at) {
+  if (ctrl->flat) {
+    if (threadIdx.x == 0) plan[0] = -1;
+    return;  // uniform
+  }
   __shared__ float red[3][kPlanThreads / 64];
   __shared__ int32_t wsum[kPlanThreads / 64];
   int32_t* rec = plan + rec_at;
@@ -950,7 +1049,7 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
     const int m = seed_samples(n, (int)p.d);
     int tps = 2;  // threads per sample
     while (m * tps * 2 <= kSeedThreads && tps < 64) tps *= 2;
-    const size_t lds = sizeof(float) * (size_t)m * (size_t)(p.d + 1);
+    const size_t lds = sizeof(float) * (size_t)m * (size_t)seed_stride((int)p.d);
     // (The attribute is the function's, not the call's: its bound, whatever this
     // call needs, so that calls of other threads stay within it.)
     hipError_t e = hipFuncSetAttribute((const void*)pivot_seed_kernel,
@@ -958,7 +1057,7 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
                                        (int)(sizeof(float) * kSeedFloats));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
-                       m, tps, a.mu32, a.ctrl, p.scale_exp, srow);
+                       m, tps, a.mu32, a.ctrl, p.scale_exp, a.plan ? 1 : 0, a.pdist, srow);
     hipLaunchKernelGGL(assign_pivot_kernel, dim3(ga), dim3(kAssignThreads),
                        sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.mu32,
                        a.ctrl, p.scale_exp, srow, a.pdist, a.lab);
@@ -1025,9 +1124,9 @@ hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t st) {
   const auto grid = [](int64_t boxes) { return dim3((unsigned)((boxes * 2 * kBoxDim + 255) / 256)); };
   const int64_t chunks = (stages + 63) / 64;
   hipLaunchKernelGGL(stage_box_kernel, grid(stages), dim3(256), 0, st, a.box32, subs, stages,
-                     p.stage_rows / 32, a.sbox);
+                     p.stage_rows / 32, a.ctrl, a.sbox);
   hipLaunchKernelGGL(stage_box_kernel, grid(chunks), dim3(256), 0, st, a.sbox, stages, chunks, 64,
-                     a.xbox);
+                     a.ctrl, a.xbox);
   return hipGetLastError();
 }
 
@@ -1037,10 +1136,10 @@ hipError_t launch_plan(const Plan& p, const Args& a, int64_t q_begin, int64_t q_
   const int64_t stages = (p.nr + p.stage_rows - 1) / p.stage_rows;
   hipLaunchKernelGGL(plan_estimate_kernel, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st,
                      a.box32, a.sbox, stages, q_begin / 32, (q_rows + 31) / 32, p.tile_rows / 32,
-                     tiles, p.prune, a.plan + a.plan_tiles);
+                     tiles, p.prune, a.ctrl, a.plan + a.plan_tiles);
   hipLaunchKernelGGL(plan_pieces_kernel, dim3(1), dim3(kPlanThreads), 0, st, tiles, stages, slots,
                      cus, (int)a.plan_cap, 1024.0f * p.kprime / p.stage_rows,
-                     200.0f * p.kprime / p.stage_rows, a.plan, a.plan_tiles);
+                     200.0f * p.kprime / p.stage_rows, a.ctrl, a.plan, a.plan_tiles);
   return hipGetLastError();
 }
 

@@ -111,7 +111,7 @@ struct Ctrl {
   uint32_t internal;        // set when a kernel finds an inconsistency it cannot recover from
   uint64_t fold_max_bits;   // max over references of the folded seed's error, fp64 bits
   uint32_t bad_label;       // classifier: a reference label outside [0, n_classes)
-  uint32_t pad0;
+  uint32_t flat;            // the pivots cannot tell the rows apart: plain scan (order.hip)
   // NWR: candidate pairs recomputed exactly, as kUncParts partial counts
   // 128 bytes apart (the total is their sum).  Atomics on one address from
   // every wave serialise: at 3 x 10^4 rows they took as long as the rest of
