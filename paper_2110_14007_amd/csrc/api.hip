@@ -44,8 +44,12 @@ constexpr int32_t kMaxTailParts = 8;
 constexpr int64_t kTailLists = 1 << 18;
 // Smallest query block of a pruned scan whose tiles cannot be cut (prune_block).
 constexpr int64_t kUncutRows = 1 << 17;
-// X against X from this many rows on runs the pruned scan (one split in its
-// order).  Rows of more than 16 elements: below, more splits are the safer choice
+// Smallest query block of a pruned scan (64 workgroups and their extra pieces).
+// 100,000 rows against themselves, time over that of the splits: blocks of 1,024
+// 1.0 to 1.7 of five kinds of rows, of 4,096 0.41 to 1.25, of 8,192 0.45 to 0.95 where
+// the boxes rule rows out.
+constexpr int64_t kPruneMinBlock = 8192;
+// X against X from this many rows on runs the pruned scan.  Rows of more than 16 elements: below, more splits are the safer choice
 // (at 62,000 rows clustered ones take 0.51 to 0.68 of the two splits' time,
 // unclustered ones at most 1.04 of it; at 38,000 unclustered ones up to 1.56).
 // Shorter rows: boxes of columns rule less out the more columns there are, until
@@ -121,6 +125,13 @@ int64_t auto_splits(int64_t qb, int64_t nr, int64_t kp) {
   return s < 1 ? 1 : s;
 }
 
+// Splits of the plain scan that stands by for a pruned one: none from two thirds of a
+// round of workgroups on, in the grouped order (normal rows of 32, blocks of 49,152:
+// 0.82 of two splits' time; of 32,768: 1.2).
+static int64_t plain_splits(int64_t qb, int64_t nr, int64_t kp) {
+  return qb >= (kp >= 64 ? 171 : 342) * 128 ? 1 : auto_splits(qb, nr, kp);
+}
+
 // Splits of a range query (no lists to fill), and of a caller's query block whose
 // workspace is too small for auto_splits: two waves per SIMD, at least 2048
 // references each, at most 16.
@@ -171,19 +182,31 @@ static void set_order_tail(Plan* p, const tod_options& o) {
   // group on); by default from kOrderMinRows references on.
   const bool want = o.reorder > 0 || (o.reorder == 0 && p->nr >= kOrderMinRows);
   // (With runs, the tile scans the whole set in pieces whatever S is.)
-  p->order = (p->self && p->tile_kind == 1 && (p->splits == 1 || p->runs > 1) && want) ? 1 : 0;
+  // (With the pruned scan, in blocks of less than a round, S is the plain scan's.)
+  p->order = (p->self && p->tile_kind == 1 &&
+              (p->splits == 1 || p->runs > 1 || p->split_order) && want)
+                 ? 1
+                 : 0;
   // Tail split of the register-list tile with one reference split (not with
   // runs: their pieces already halve every workgroup's scan).
   p->tail_parts = 1;
   p->tail_auto = 0;
   p->tail_lists = 0;
-  if (p->tile_kind == 1 && p->splits == 1 && p->runs == 1 && o.tail_parts != 1) {
+  if (p->tile_kind == 1 && (p->splits == 1 || (p->split_order && p->order)) && p->runs == 1 &&
+      o.tail_parts != 1) {
     p->tail_parts = o.tail_parts == 0 ? kMaxTailParts : o.tail_parts;
     p->tail_auto = o.tail_parts == 0 ? 1 : 0;
     const int64_t want_lists = p->query_block * p->tail_parts;
     p->tail_lists = want_lists < kTailLists ? want_lists : kTailLists;
   }
   set_prune(p, p->order ? prune_kind(*p, o) : kPruneNone);
+}
+
+// The same splits without the pruned scan.
+static void drop_prune(Plan* p, const tod_options& o) {
+  p->split_order = 0;
+  set_order_tail(p, o);
+  set_prune(p, kPruneNone);
 }
 
 tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, int32_t self,
@@ -244,11 +267,18 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   if (qb > p->nq_pad) qb = p->nq_pad;
   p->query_block = qb;
   p->blocks = (nq + qb - 1) / qb;
-  // (The pruned scan of X against X cuts its own work: one split.)
+  // (The pruned scan of X against X cuts its own work; the splits are those of the
+  // plain scan that takes over where the boxes rule too little out.  Rows of 9 to 16
+  // elements often do, and their k-d order does not suit splits: one split or none.)
   const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
                       prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
-                      (nr >= prune_rows(d) || o.reorder > 0);
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits : pruned ? 1 : auto_splits(qb, nr, kp));
+                      (o.reorder > 0 ||
+                       (nr >= prune_rows(d) && qb >= kPruneMinBlock &&
+                        (d <= 8 || d > kBoxDim || plain_splits(qb, nr, kp) == 1)));
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits
+                : pruned         ? plain_splits(qb, nr, kp)
+                                 : auto_splits(qb, nr, kp));
+  p->split_order = pruned && p->splits > 1 ? 1 : 0;
   p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
   // operand fits in registers and whose shortlist is 16, 32 or 64 long.  Rows
@@ -381,7 +411,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   // The pruned scan's boxes go first: the same plan without them.
   if (p->prune) {
     Plan q = *p;
-    set_prune(&q, kPruneNone);
+    drop_prune(&q, o);
     if (make_layout(q).total <= ws_bytes) {
       *p = q;
       return TOD_OK;
@@ -394,8 +424,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
     for (int64_t s = most > wide ? most : wide; s >= 1; --s) {
       Plan q = *p;
       set_splits(&q, s);
-      set_order_tail(&q, o);
-      set_prune(&q, kPruneNone);
+      drop_prune(&q, o);
       if (make_layout(q).total <= ws_bytes) {
         *p = q;
         return TOD_OK;
@@ -412,7 +441,11 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   q.tail_auto = 0;
   q.tail_lists = 0;
   for (int with_prune = q.prune && prune_block(q) ? 1 : 0; with_prune >= 0; --with_prune) {
-    if (!with_prune) set_prune(&q, kPruneNone);
+    if (!with_prune) {
+      set_prune(&q, kPruneNone);
+      q.order = q.order && !q.split_order;
+      q.split_order = 0;
+    }
     if (make_layout(q).total <= ws_bytes) {
       *p = q;
       return TOD_OK;

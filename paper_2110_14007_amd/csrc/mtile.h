@@ -880,7 +880,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     st0 = uniform(st0);
     hs = uniform(hs);
   } else {
-    if (a.cstart) {
+    if (a.cstart && a.splits == 1) {
       // The last group starting at or before p0 (starts ascend; an empty group
       // shares its start with the next one).
       if (a.substart) {
@@ -1335,13 +1335,16 @@ hipError_t launch_mtile_pr(const Plan& p, const Args& a, int64_t q_begin, int64_
     if (e != hipSuccess) return e;
     // Planned pieces: the tiles, then as many workgroups as there is room for
     // extra pieces (those past the plan's count leave at once).
-    hipLaunchKernelGGL(kern, dim3((unsigned)(wgs + a.plan_cap)), dim3(W * 64), lds, st, a, q_begin,
+    Args b = a;  // (the splits are the plain scan's)
+    b.splits = 1;
+    b.split_len = a.nr;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(wgs + a.plan_cap)), dim3(W * 64), lds, st, b, q_begin,
                        q_rows);
     return hipGetLastError();
   }
   int64_t main_wgs = wgs;
   int parts = 1;
-  if (occ) {
+  if (occ && p.splits == 1) {
     const int64_t slots = (int64_t)cus * per;
     const int64_t tw = wgs % slots;
     const int64_t trows = q_rows - (wgs - tw) * QW;

@@ -132,8 +132,10 @@ __device__ __forceinline__ float scaled_elem(float x, float mu, double s) {
 // no more than that: on Gaussian and uniform rows of 17 to 256 elements the share
 // was 0.85 and more (boxes: 0.998 and more), on ten or five clusters 0.09 to 0.22
 // (0.14 to 0.38), on a curved sheet 0.16 to 0.22 (0.45 to 0.54).  From kFlatShare
-// on the call keeps to evenly spaced seeds, input order within their groups and
-// the plain scan: pivots and distance bins made that 3 to 15 % slower there (their
+// on the call keeps to the plain scan over evenly spaced seeds, input order within
+// their groups (in several splits: over the rows in input order, whose splits are
+// all alike: 100,000 normal rows of 32 in blocks of 8,192 took 1.2 times as long in
+// eight pieces of the grouped order): pivots and distance bins made that 3 to 15 % slower there (their
 // order puts the outliers into tiles of their own, and a group's rows in the order
 // of their distance, not at random, fill the lists more often).
 constexpr int kFlatQueries = 32;
@@ -155,7 +157,7 @@ int seed_samples(int64_t n, int d) {
 __global__ void __launch_bounds__(kSeedThreads)
 pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
                   const float* __restrict__ mu32, Ctrl* __restrict__ ctrl, int scale_exp,
-                  int may_flat, float* __restrict__ dist, int32_t* __restrict__ srow) {
+                  int flat_as, float* __restrict__ dist, int32_t* __restrict__ srow) {
   extern __shared__ __align__(16) float smp[];  // [m][stride], centred and scaled
   __shared__ float wsum[kSeedThreads / 64];
   __shared__ int32_t rows[kSeedSamples], piv[kPivots];
@@ -205,7 +207,7 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
     }
     for (int off = 1; off < tps; off <<= 1) acc += __shfl_xor(acc, off, 64);
     near = fminf(near, acc);
-    if (may_flat && i < m && sub == 0) dist[(int64_t)i * kPivots + c] = sqrtf(acc);
+    if (flat_as && i < m && sub == 0) dist[(int64_t)i * kPivots + c] = sqrtf(acc);
     // Inclusive sums of the weights in sample order.
     float incl = i < m && sub == 0 ? near : 0.0f;
     for (int off = 1; off < 64; off <<= 1) {
@@ -229,7 +231,7 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
     __syncthreads();  // every thread has read pick before it is reset
     if (tid == 0) pick = m - 1;
   }
-  if (!may_flat) {  // uniform
+  if (!flat_as) {  // uniform
     if (tid < kPivots) srow[tid] = piv[tid];
     return;
   }
@@ -271,7 +273,7 @@ pivot_seed_kernel(const float* __restrict__ x, int64_t n, int d, int m, int tps,
   __syncthreads();
   const bool flat = cnt[0] > 0 && (float)cnt[1] >= kFlatShare * (float)cnt[0];
   if (tid < kPivots) srow[tid] = flat ? (int32_t)((int64_t)tid * n / kPivots) : piv[tid];
-  if (tid == 0) ctrl->flat = flat ? 1u : 0u;
+  if (tid == 0) ctrl->flat = flat ? (uint32_t)flat_as : 0u;
 }
 
 // Longer rows with the pruned scan: groups by the nearest pivot.  Per row the
@@ -295,6 +297,10 @@ assign_pivot_kernel(const float* __restrict__ x, int64_t n, int d,
   __syncthreads();
   const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= n) return;
+  if (ctrl->flat == 2) {  // input order
+    lab[row] = 0;
+    return;
+  }
   float acc[kPivots];
 #pragma unroll
   for (int c = 0; c < kPivots; ++c) acc[c] = 0.0f;
@@ -1057,7 +1063,7 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
                                        (int)(sizeof(float) * kSeedFloats));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
-                       m, tps, a.mu32, a.ctrl, p.scale_exp, a.plan ? 1 : 0, a.pdist, srow);
+                       m, tps, a.mu32, a.ctrl, p.scale_exp, !a.plan ? 0 : p.splits > 1 ? 2 : 1, a.pdist, srow);
     hipLaunchKernelGGL(assign_pivot_kernel, dim3(ga), dim3(kAssignThreads),
                        sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.mu32,
                        a.ctrl, p.scale_exp, srow, a.pdist, a.lab);

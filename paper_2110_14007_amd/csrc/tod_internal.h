@@ -43,6 +43,8 @@ struct Plan {
   int32_t lists;       // int32 / fp64 neighbour lists kept in the workspace (LOF, score
                        // aggregates, classifier)
   int32_t order;       // 1: grouped scan order (order.hip), X against X only
+  int32_t split_order = 0;  // 1: the order and the pruned scan with several splits, which the
+                            // plain scan that may take over uses
   int32_t groups;      // counting-sort keys of the grouped order (order_groups)
   int32_t prune = 0;   // kPruneNone, or the kind of the boxes the register-list tile skips
                        // reference stages by (grouped order only)
@@ -111,7 +113,8 @@ struct Ctrl {
   uint32_t internal;        // set when a kernel finds an inconsistency it cannot recover from
   uint64_t fold_max_bits;   // max over references of the folded seed's error, fp64 bits
   uint32_t bad_label;       // classifier: a reference label outside [0, n_classes)
-  uint32_t flat;            // the pivots cannot tell the rows apart: plain scan (order.hip)
+  uint32_t flat;            // the pivots cannot tell the rows apart: plain scan, over evenly spaced
+                            // seeds' groups (1) or in input order (2; order.hip)
   // NWR: candidate pairs recomputed exactly, as kUncParts partial counts
   // 128 bytes apart (the total is their sum).  Atomics on one address from
   // every wave serialise: at 3 x 10^4 rows they took as long as the rest of

@@ -67,6 +67,11 @@ def data(kind, n, d, rng):
     ("two", 21000, 1, 3, {}),
     ("two", 21000, 5, 20, {}),
     ("clusters", 70, 5, 4, {"ref_splits": 1}),
+    # blocks of less than a round of workgroups: the plain scan that takes over has splits
+    ("clusters", 30011, 20, 10, {"query_block": 8192}),
+    ("uniform", 30011, 20, 10, {"query_block": 8192}),
+    ("uniform", 20011, 300, 12, {"query_block": 512}),
+    ("two", 30000, 7, 20, {"query_block": 2048}),
     # scans that may not be cut, and ones cut in a region of another size
     ("clusters", 131105, 20, 10, {"tail_parts": 1}),
     ("clusters", 20011, 40, 10, {"tail_parts": 8, "ref_splits": 1, "query_block": 4096}),

@@ -206,6 +206,21 @@ def test_one_block_in_few_splits(tod, mode, nq, nr, d, k, prec):
         assert p["blocks"] == 1
 
 
+# Small query blocks of a set against itself keep the splits that fill the GPU: the
+# pruned scan needs blocks of 8,192 rows, and below a round of workgroups the plain
+# scan that may take over from it has splits.
+@pytest.mark.parametrize("d", [6, 32, 200])
+@pytest.mark.parametrize("qb", [32, 128, 1024, 4096, 8192, 16384, 32768, 65536])
+def test_small_blocks_of_a_large_set(tod, d, qb):
+    n = 100_000
+    p = tod.tod_plan(n, n, d, 10, tod.options(query_block=qb, exclude_self=True))
+    assert p["reordered"] == (qb >= 8192)
+    assert (qb // 128 or 1) * p["ref_splits"] >= (256 if qb < 65536 else 512) or \
+        p["ref_splits"] >= 32
+    assert p["ref_splits"] == tod.tod_plan(n, n, d, 10, tod.options(
+        query_block=qb, exclude_self=True, reorder=-1))["ref_splits"]
+
+
 # The pivot distances lie over the partial lists: a block shrunk to the workspace
 # counts them once.
 @pytest.mark.parametrize("n,d,k,share", [(2797960, 98, 1, 0.95), (2797960, 98, 1, 0.9),
