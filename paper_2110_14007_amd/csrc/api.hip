@@ -102,36 +102,6 @@ tod_status check_sizes(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t exc
 
 namespace tod {
 
-// Reference splits for a query block of qb rows (Section 6 customised cdist
-// batching): enough waves for two per SIMD on 256 CUs x 4 SIMDs (one per SIMD
-// with lists of 64 entries and more, whose kernels hold one), rounded down so
-// that no second round of workgroups follows, but at least 8 K' references per
-// split, and at most 64.  Every split fills its own K' list per query, but while
-// the GPU has idle compute units that runs beside the other splits: what counts
-// is the length of one wave's scan.  (At 2,000 x 16, k = 10, the tile takes 54 us
-// in seven splits, 82 in one; 64 queries against 50,000 x 32 took 145 us in the
-// 16 splits that 2,048 rows each allowed.)
-int64_t auto_splits(int64_t qb, int64_t nr, int64_t kp) {
-  // (In workgroups of four waves.)
-  const int64_t groups = (qb + 127) / 128, target = kp >= 64 ? 256 : 512;
-  int64_t s = target / groups;
-  // (Kernels with 16-entry lists hold more waves: few splits round up.  22,000 x
-  // 8 against itself took 0.82 of its speed in two splits instead of three; with
-  // 32 entries two are the faster ones, by a fifth.)
-  if (s < 2 || (kp <= 16 && s < 4)) s = (target + groups - 1) / groups;
-  const int64_t cap = nr / (8 * kp) > 1 ? nr / (8 * kp) : 1;
-  if (s > cap) s = cap;
-  if (s > 64) s = 64;
-  return s < 1 ? 1 : s;
-}
-
-// Splits of the plain scan that stands by for a pruned one: none from two thirds of a
-// round of workgroups on, in the grouped order (normal rows of 32, blocks of 49,152:
-// 0.82 of two splits' time; of 32,768: 1.2).
-static int64_t plain_splits(int64_t qb, int64_t nr, int64_t kp) {
-  return qb >= (kp >= 64 ? 171 : 342) * 128 ? 1 : auto_splits(qb, nr, kp);
-}
-
 // Splits of a range query (no lists to fill), and of a caller's query block whose
 // workspace is too small for auto_splits: two waves per SIMD, at least 2048
 // references each, at most 16.
@@ -142,6 +112,67 @@ static int64_t long_splits(int64_t qb, int64_t nr) {
   if (s > cap) s = cap;
   if (s > 16) s = 16;
   return s < 1 ? 1 : s;
+}
+
+// Reference splits for a query block of qb rows (Section 6 customised cdist
+// batching), by how many of the kernel's workgroups the GPU runs at once: at least
+// 8 K' references per split, and at most 64.  Every split fills its own K' list
+// per query, but while the GPU has idle compute units that runs beside the other
+// splits: what counts is the length of one wave's scan.
+//
+// Register-list kernel: as many splits as fit in one round.  A second round that is
+// not full costs more than it gives, also in place of one round that is a good half
+// full (50,000 references of 8 to 512 columns, K' = 32: 10,000 queries 6 splits,
+// the next best 1.08 to 1.3 times as long, 7 splits 1.3 to 1.6; 30,000 queries 2,
+// three 1.25 to 1.4; 40,000 queries 1, two 1.11 to 1.32.  K' = 16 on 8 columns:
+// 10,000 queries 12 splits, six 1.25 to 1.4).  Two runs (K' = 128) already cut every
+// split in two.  With few pieces more rows fail the certificate, most in the
+// grouped order, whose pieces hold a row's neighbours together: X against X keeps
+// long_splits at least (40,000 x 200 in blocks of 8,192: 11.7 ms in 8 splits, 90 in
+// 4), other calls two (13,000 against 30,000 x 512, k = 100: 2.05 ms, in one 2.9).
+//
+// LDS-list kernel (no tail split): the S with the shortest rounds, counting the
+// rows a wave could scan in the time it takes to fill its lists.  That time is
+// about 8.6 us for each of the K' entries (measured at K' = 64 to 256 on 32 to 700
+// columns), a reference row's 0.03 us + 0.0008 us a column, in fp32 0.0055 us a
+// column.  (50,000 x 32, K' = 128: 1,500 queries take 1.14 ms in 16 splits, 1.83 in
+// 21, which no longer fit in one round; 14,000 take 4.0 in one, 5.3 in two or five;
+// 30,000 x 700, K' = 64: 20,000 take 24 ms in one, 17 in three.)
+static int64_t auto_splits(const Plan& p, int64_t qb) {
+  constexpr int64_t kCus = 256;
+  const int64_t kp = p.kprime;
+  int64_t cap = p.nr / (8 * kp) > 1 ? p.nr / (8 * kp) : 1;
+  if (cap > 64) cap = 64;
+  int64_t s = 1;
+  if (p.tile_kind == 1) {
+    const int32_t r = (int32_t)kp / p.runs / 2;
+    const int64_t rows = 32 * mt::tile_waves(p.dpad_t, p.fold, r, false) *
+                         mt::query_groups(p.dpad_t, p.fold, r);
+    s = kCus * mt::tile_resident(p.dpad_t, p.fold, r) / ((qb + rows - 1) / rows) / p.runs;
+    int64_t least = p.runs > 1 ? long_splits(qb, p.nr) : 1;
+    if (!p.self && least > 2) least = 2;
+    if (s < least) s = least;
+    return s < cap ? s : cap;
+  }
+  const int w = tile::tile_waves((int)kp);
+  const int64_t wgs = (qb + 32 * w - 1) / (32 * w);
+  const bool whole = p.dpad_t > 0 && (p.precision == TOD_PREC_FP32 || p.dpad_t <= 128);
+  const size_t lds =
+      tile::lds_bytes(whole ? p.dpad_t : p.dpad, p.esize, (int)kp, w, whole);
+  const int64_t slots = kCus * (int64_t)(160 * 1024 / lds);
+  const double row_us = p.precision == TOD_PREC_FP32 ? 0.0055 * (double)p.d
+                                                     : 0.03 + 0.0008 * (double)p.d;
+  const double fill = 8.6 * (double)kp / row_us;
+  double best = INFINITY;
+  for (int64_t c = 1; c <= cap; ++c) {
+    const double rounds = (double)((wgs * c + slots - 1) / slots);
+    const double t = rounds * ((double)p.nr / (double)c + fill);
+    if (t < best) {
+      best = t;
+      s = c;
+    }
+  }
+  return s;
 }
 
 // S splits of 32-row multiples (fewer if the rounding leaves some empty).
@@ -267,19 +298,7 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
   if (qb > p->nq_pad) qb = p->nq_pad;
   p->query_block = qb;
   p->blocks = (nq + qb - 1) / qb;
-  // (The pruned scan of X against X cuts its own work; the splits are those of the
-  // plain scan that takes over where the boxes rule too little out.  Rows of 9 to 16
-  // elements often do, and their k-d order does not suit splits: one split or none.)
-  const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
-                      prec != TOD_PREC_FP32 && d <= 512 && kp <= 64 &&
-                      (o.reorder > 0 ||
-                       (nr >= prune_rows(d) && qb >= kPruneMinBlock &&
-                        (d <= 8 || d > kBoxDim || plain_splits(qb, nr, kp) == 1)));
-  set_splits(p, o.ref_splits > 0 ? o.ref_splits
-                : pruned         ? plain_splits(qb, nr, kp)
-                                 : auto_splits(qb, nr, kp));
-  p->split_order = pruned && p->splits > 1 ? 1 : 0;
-  p->waves_per_group = kp <= 32 ? 4 : (kp == 64 ? 2 : 1);
+  p->waves_per_group = tile::tile_waves((int)kp);
   // The register-list MFMA kernel covers fp16 / bf16 filters whose query
   // operand fits in registers and whose shortlist is 16, 32 or 64 long.  Rows
   // of at most 8 elements carry the accumulator seed -N_j/2 in their padding
@@ -320,6 +339,16 @@ tod_status make_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t lof, 
       }
     }
   }
+  // (The pruned scan of X against X cuts its own work; the splits are those of the
+  // plain scan that takes over where the boxes rule too little out.  Rows of 9 to 16
+  // elements often do, and their k-d order does not suit splits: one split or none.)
+  const int64_t splits = auto_splits(*p, qb);
+  const bool pruned = self && o.ref_splits == 0 && o.reorder >= 0 && o.tail_parts == 0 &&
+                      p->tile_kind == 1 && p->runs == 1 &&
+                      (o.reorder > 0 || (nr >= prune_rows(d) && qb >= kPruneMinBlock &&
+                                         (d <= 8 || d > kBoxDim || splits == 1)));
+  set_splits(p, o.ref_splits > 0 ? o.ref_splits : splits);
+  p->split_order = pruned && p->splits > 1 ? 1 : 0;
   if (p->tile_kind == 1) {
     const int32_t r = (int32_t)kp / p->runs / 2;
     // (A box holds at least kUnitRows rows.)
@@ -419,7 +448,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
   }
   // The same block in fewer, longer splits, down to one (in the grouped order).
   if (o.ref_splits == 0) {
-    const int64_t most = auto_splits(p->query_block, p->nr, p->kprime);
+    const int64_t most = auto_splits(*p, p->query_block);
     const int64_t wide = long_splits(p->query_block, p->nr);
     for (int64_t s = most > wide ? most : wide; s >= 1; --s) {
       Plan q = *p;
@@ -490,7 +519,7 @@ tod_status fit_plan(Plan* p, size_t ws_bytes, const tod_options& o, std::string*
     need = shape(&f, 32, 1);
     const int64_t qb = largest(&f);
     if (qb == 0) continue;
-    int64_t s = auto_splits(qb, f.nr, f.kprime);
+    int64_t s = auto_splits(f, qb);
     if (with_order == 2) {
       Plan g = f;
       set_prune(&g, kPruneNone);

@@ -33,5 +33,12 @@ constexpr int query_groups(int dpad, bool fold, int r) {
   return dpad >= 512 && !fold && r <= 16 ? 2 : 1;
 }
 
+// Workgroups of the plain scan that a compute unit holds at once.
+constexpr int tile_resident(int dpad, bool fold, int r) {
+  return r >= 32 || tile_waves(dpad, fold, r, false) > 4 || query_groups(dpad, fold, r) > 1 ? 1
+         : r <= 8 && (dpad == 16 || dpad == 64 || dpad == 128)                             ? 3
+                                                                                           : 2;
+}
+
 }  // namespace mt
 }  // namespace tod

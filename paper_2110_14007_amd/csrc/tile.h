@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "halfwave.h"
+#include "tile_shape.h"
 #include "tod_internal.h"
 #include "wave.h"
 
@@ -36,9 +37,6 @@ namespace tile {
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-constexpr int kQH = 16;       // queue slots per (query, half-wave)
-constexpr int kQ = 2 * kQH;   // queue slots per query
 
 template <int PREC>
 struct Elem;
@@ -82,20 +80,6 @@ __device__ __forceinline__ int tile_row(int r, int lane) {
     // 32x32 MFMA accumulator layout: column = lane % 32, rows as below.
     return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
   }
-}
-
-__host__ __device__ constexpr int row_bytes(int dpad, int es) { return dpad * es + 16; }
-
-// Rows longer than the register-operand shapes are staged in column slabs of
-// kSlabBytes per row (32 rows per slab), so LDS use does not grow with d:
-// at most 33 KiB of slab plus the lists (K' = 256: 72 KiB) per workgroup.
-constexpr int kSlabBytes = 1024;
-
-// LDS bytes of the tile kernel for these parameters (host and device agree).
-// dbuf: the double-buffered whole-row staging of the register-operand shapes.
-__host__ __device__ constexpr size_t lds_bytes(int dpad, int es, int kp, int w, bool dbuf) {
-  return (dbuf ? (size_t)2 * 32 * row_bytes(dpad, es) : (size_t)32 * (kSlabBytes + 16)) + 256 +
-         (size_t)w * 32 * (kp + kQ) * sizeof(uint64_t);
 }
 
 // Merge the queues of the queries in `qmask` (bit q = query q of this wave)
@@ -459,11 +443,11 @@ template <int PREC>
 hipError_t launch_prec(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows,
                        hipStream_t st) {
   switch (p.kprime) {
-    case 16: return launch_kp<PREC, 16, 4>(p, a, q_begin, q_rows, st);
-    case 32: return launch_kp<PREC, 32, 4>(p, a, q_begin, q_rows, st);
-    case 64: return launch_kp<PREC, 64, 2>(p, a, q_begin, q_rows, st);
-    case 128: return launch_kp<PREC, 128, 1>(p, a, q_begin, q_rows, st);
-    case 256: return launch_kp<PREC, 256, 1>(p, a, q_begin, q_rows, st);
+    case 16: return launch_kp<PREC, 16, tile_waves(16)>(p, a, q_begin, q_rows, st);
+    case 32: return launch_kp<PREC, 32, tile_waves(32)>(p, a, q_begin, q_rows, st);
+    case 64: return launch_kp<PREC, 64, tile_waves(64)>(p, a, q_begin, q_rows, st);
+    case 128: return launch_kp<PREC, 128, tile_waves(128)>(p, a, q_begin, q_rows, st);
+    case 256: return launch_kp<PREC, 256, tile_waves(256)>(p, a, q_begin, q_rows, st);
     default: return hipErrorInvalidValue;
   }
 }

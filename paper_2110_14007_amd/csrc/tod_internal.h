@@ -10,6 +10,7 @@
 
 #include "../../include/tod.h"
 #include "mtile_shape.h"
+#include "tile_shape.h"
 
 namespace tod {
 

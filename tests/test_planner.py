@@ -221,6 +221,34 @@ def test_small_blocks_of_a_large_set(tod, d, qb):
         query_block=qb, exclude_self=True, reorder=-1))["ref_splits"]
 
 
+# Splits fill one round of the kernel's workgroups and start no second one, where a
+# compute unit holds 1 to 3 of them (by the list's length, the row's and the
+# precision); two runs over the grouped order keep the pieces the certificate needs.
+@pytest.mark.parametrize("nq,nr,d,k,prec,per_cu,rows", [
+    (10000, 50000, 8, 5, "auto", 1, 512), (10000, 50000, 16, 5, "auto", 3, 128),
+    (10000, 50000, 32, 5, "auto", 2, 128), (10000, 50000, 64, 5, "auto", 3, 128),
+    (10000, 50000, 64, 20, "auto", 1, 256), (30000, 50000, 128, 20, "auto", 2, 128),
+    (40000, 50000, 300, 10, "auto", 2, 128), (20000, 50000, 512, 10, "auto", 1, 256),
+    (20000, 50000, 32, 50, "auto", 1, 128),
+    # the LDS-list kernel: K' = 128 and 256, fp32, rows beyond 512 columns
+    (1500, 50000, 32, 100, "auto", 3, 32), (4000, 50000, 32, 100, "fp32", 3, 32),
+    (2500, 50000, 16, 200, "auto", 2, 32), (3000, 40000, 32, 20, "fp32", 2, 128),
+    (3000, 30000, 700, 10, "auto", 1, 128), (1000, 30000, 700, 50, "auto", 1, 64),
+])
+def test_splits_fill_one_round(tod, nq, nr, d, k, prec, per_cu, rows):
+    p = tod.tod_plan(nq, nr, d, k, tod.options(precision=prec))
+    groups = p["ref_splits"] * -(-nq // rows)
+    assert groups <= 256 * per_cu or p["ref_splits"] == 1
+    assert groups + -(-nq // rows) > 256 * per_cu * 0.9
+
+
+def test_two_runs_keep_their_splits(tod):
+    for qb, least in ((1024, 16), (8192, 8), (32768, 2)):
+        p = tod.tod_plan(40000, 40000, 200, 64, tod.options(query_block=qb, exclude_self=True))
+        assert p["list_runs"] == 2 and p["ref_splits"] >= least
+    assert tod.tod_plan(13000, 30000, 512, 100)["ref_splits"] == 2
+
+
 # The pivot distances lie over the partial lists: a block shrunk to the workspace
 # counts them once.
 @pytest.mark.parametrize("n,d,k,share", [(2797960, 98, 1, 0.95), (2797960, 98, 1, 0.9),
