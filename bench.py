@@ -115,7 +115,8 @@ def cpu_baseline(x, k, rows, lof_full=False):
 # Sources that decide what the tile kernels execute: the kernels themselves,
 # their shared headers and the planner that picks their template arguments.
 TILE_SOURCES = ("api.hip", "tod_internal.h", "wave.h", "halfwave.h", "tile.h", "tile_f32.hip",
-                "tile_f16.hip", "tile_bf16.hip", "mtile.h", "mtile_f16.hip", "mtile_bf16.hip",
+                "tile_f16.hip", "tile_bf16.hip", "tile_shape.h", "mtile_shape.h",
+                "mtile.h", "mtile_f16.hip", "mtile_bf16.hip",
                 "order.hip", "rtile.h", "rtile_f16.hip", "rtile_bf16.hip", "nwr.hip", "loci.hip")
 
 

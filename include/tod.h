@@ -116,7 +116,8 @@ typedef struct {
  * row, k + 8 first and then 16 more at a time up to K', so rows_certified and
  * rows_fallback carry what a single maximum would summarise.) */
 typedef struct {
-  uint32_t struct_size;   /* must be sizeof(tod_stats) */
+  uint32_t struct_size;   /* sizeof(tod_stats), or TOD_STATS_SIZE_1 (without the last three
+                           * fields, which such a call leaves alone) */
   int32_t precision;      /* resolved tod_precision */
   int32_t kprime;         /* shortlist length K' */
   int32_t ref_splits;     /* S */
@@ -124,8 +125,8 @@ typedef struct {
   int64_t blocks;         /* number of query blocks */
   int64_t rows_certified; /* rows whose shortlist passed the certificate */
   int64_t rows_fallback;  /* rows recomputed exactly */
-  int64_t tile_launches;  /* launches of the fused distance + selection kernel (a block with a
-                           * tail split takes two) */
+  int64_t tile_launches;  /* launches of the fused distance + selection kernel that scanned
+                           * references (a block with a tail split takes two) */
   float ms_prep, ms_tile, ms_recheck, ms_fallback, ms_score, ms_total;
                           /* ms_recheck includes the merge of the split lists, which runs
                            * inside the recheck kernel (there is no separate ms_merge) */
@@ -139,7 +140,15 @@ typedef struct {
   int32_t list_runs;       /* 2 if each shortlist was built as two runs of K'/2 entries (the
                             * register-list tile over two pieces of the scan order: K' = 128
                             * on rows of 129..512 elements), else 1 */
+  int32_t pruned_kind;     /* boxes of the pruned scan (see tod_options.reorder): 0 none, 1
+                            * distances to pivots, 2 columns */
+  int64_t pruned_blocks;   /* query blocks that the pruned scan ran; the others' boxes ruled out
+                            * too little, and the plain scan took over */
+  int64_t pairs_scanned;   /* kNN calls: (query, reference) pairs whose key the filter computed,
+                            * counted by 32 queries and 128 references in the pruned scan */
 } tod_stats;
+/* (pruned_kind lies in the padding that ended the first layout.) */
+#define TOD_STATS_SIZE_1 ((uint32_t)offsetof(tod_stats, pruned_blocks))
 
 /* Fill *opts with defaults: AUTO precision (the fp16 filter of Section 5.2's
  * provable quantization), planner-chosen K', query block and splits

@@ -85,6 +85,11 @@ tod_status resolve_options(const tod_options* in, tod_options* out) {
   return TOD_OK;
 }
 
+// Callers built against the first layout of tod_stats stay welcome.
+bool stats_size_ok(const tod_stats* s) {
+  return !s || s->struct_size == sizeof(tod_stats) || s->struct_size == TOD_STATS_SIZE_1;
+}
+
 tod_status check_sizes(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t excl) {
   if (nq <= 0 || nr <= 0) return fail(TOD_ERR_INVALID_ARG, "row counts must be positive");
   if (d <= 0) return fail(TOD_ERR_INVALID_ARG, "d must be positive");
@@ -404,7 +409,7 @@ Layout make_layout(const Plan& p) {
   } else {
     L.perm = L.lab = L.oseed = L.cstart = L.bcnt = L.boff = 0;
   }
-  L.kstart = L.box32 = L.sbox = L.xbox = L.substart = L.plan = 0;
+  L.kstart = L.box32 = L.sbox = L.xbox = L.substart = L.plan = L.ran = 0;
   if (p.prune) {
     const size_t subs = (size_t)(p.nr_pad / 32);
     const size_t stages = (size_t)((p.nr + p.stage_rows - 1) / p.stage_rows);
@@ -415,6 +420,7 @@ Layout make_layout(const Plan& p) {
     L.xbox = take(sizeof(float) * 2 * kBoxDim * ((stages + 63) / 64));
     L.substart = take(sizeof(int32_t) * subs);
     L.plan = take(sizeof(int32_t) * (size_t)plan_words((int64_t)tiles, kTailLists / p.tile_rows));
+    L.ran = take(sizeof(int32_t) * (size_t)p.blocks);
   }
   if (p.lists) {
     L.idx32 = take(sizeof(int32_t) * p.nq * p.k);
@@ -659,7 +665,7 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
   tod_status st = resolve_options(opts_in, &o);
   if (st != TOD_OK) return st;
   if (force_excl) o.exclude_self = 1;
-  if (stats && stats->struct_size != sizeof(tod_stats))
+  if (!stats_size_ok(stats))
     return fail(TOD_ERR_INVALID_ARG, "tod_stats.struct_size does not match this library");
   if (!xq || !xr) return fail(TOD_ERR_INVALID_ARG, "null input pointer");
   if (!ws) return fail(TOD_ERR_INVALID_ARG, "null workspace");
@@ -753,6 +759,7 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
       a.plan = (int32_t*)(base + L.plan);
       a.plan_cap = tod::plan_extra(p);
       a.plan_tiles = 1 + 2 * a.plan_cap;
+      a.ran = (int32_t*)(base + L.ran);
     }
   }
   a.idx32 = p.lists ? (int32_t*)(base + L.idx32) : nullptr;
@@ -777,8 +784,7 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
   hipEvent_t e_prep = tm.mark(s);
   std::vector<std::pair<hipEvent_t, hipEvent_t>> tile_ev;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> rc_ev;
-  int32_t tail_parts = 1;
-  int64_t tail_rows = 0, launches = 0;
+  std::vector<tod::TileTail> tails;  // of the plain scan, per block
   for (int64_t b = 0; b < p.blocks; ++b) {
     const int64_t q0 = b * p.query_block;
     const int64_t rows = nq - q0 < p.query_block ? nq - q0 : p.query_block;
@@ -790,11 +796,7 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
     tod::Args ar = a;
     ar.tail_q0 = tt.q0;
     ar.tail_parts = tt.parts;
-    launches += (tt.q0 > 0 ? 1 : 0) + (tt.parts > 1 ? 1 : 0);
-    if (tt.parts > 1) {
-      tail_parts = tt.parts > tail_parts ? tt.parts : tail_parts;
-      tail_rows += rows - tt.q0;
-    }
+    if (stats) tails.push_back(tt);
     he = tod::launch_recheck(p, ar, q0, rows, s);
     if (he != hipSuccess) return hip_fail(he, "recheck launch");
     hipEvent_t re = tm.mark(s);
@@ -831,9 +833,39 @@ tod_status run(const float* xq, int64_t nq, const float* xr, int64_t nr, int64_t
   tod::Ctrl host;
   he = hipMemcpyAsync(&host, a.ctrl, sizeof(host), hipMemcpyDeviceToHost, s);
   if (he != hipSuccess) return hip_fail(he, "status readback");
+  std::vector<int32_t> ran(stats ? (size_t)p.blocks : 0, p.prune && !a.plan ? 1 : 0);
+  if (stats && a.plan) {
+    he = hipMemcpyAsync(ran.data(), a.ran, sizeof(int32_t) * ran.size(), hipMemcpyDeviceToHost, s);
+    if (he != hipSuccess) return hip_fail(he, "plan readback");
+  }
   he = hipStreamSynchronize(s);
   if (he != hipSuccess) return hip_fail(he, "stream synchronize");
   if (stats) {
+    int32_t tail_parts = 1;
+    int64_t tail_rows = 0, launches = 0, pruned = 0, scanned = 0;
+    for (int64_t b = 0; b < p.blocks; ++b) {
+      const tod::TileTail& tt = tails[(size_t)b];
+      const int64_t q0 = b * p.query_block;
+      const int64_t rows = nq - q0 < p.query_block ? nq - q0 : p.query_block;
+      if (ran[(size_t)b] == 1) {
+        ++pruned;
+        ++launches;
+        continue;
+      }
+      scanned += rows * nr;
+      launches += (tt.q0 > 0 ? 1 : 0) + (tt.parts > 1 ? 1 : 0);
+      if (tt.parts > 1) {
+        tail_parts = tt.parts > tail_parts ? tt.parts : tail_parts;
+        tail_rows += rows - tt.q0;
+      }
+    }
+    for (int i = 0; i < tod::kUncParts; ++i)
+      scanned += (int64_t)host.uncertain[i * tod::kUncStride];
+    if (stats->struct_size == sizeof(tod_stats)) {
+      stats->pruned_kind = p.prune;
+      stats->pruned_blocks = pruned;
+      stats->pairs_scanned = scanned;
+    }
     stats->precision = p.precision;
     stats->kprime = p.kprime;
     stats->ref_splits = p.splits;
@@ -874,7 +906,7 @@ tod_status run_nwr(const float* xq, int64_t nq, const float* xr, int64_t nr, int
   tod_options o;
   tod_status st = resolve_options(opts_in, &o);
   if (st != TOD_OK) return st;
-  if (stats && stats->struct_size != sizeof(tod_stats))
+  if (!stats_size_ok(stats))
     return fail(TOD_ERR_INVALID_ARG, "tod_stats.struct_size does not match this library");
   if (!xq || !xr) return fail(TOD_ERR_INVALID_ARG, "null input pointer");
   if (!row_ptr_out) return fail(TOD_ERR_INVALID_ARG, "null row_ptr output");
@@ -1038,6 +1070,10 @@ tod_status run_nwr(const float* xq, int64_t nq, const float* xr, int64_t nr, int
     stats->tail_parts = 1;
     stats->tail_rows = 0;
     stats->list_runs = 1;
+    if (stats->struct_size == sizeof(tod_stats)) {
+      stats->pruned_kind = 0;
+      stats->pruned_blocks = stats->pairs_scanned = 0;
+    }
   }
   if (host.internal) return fail(TOD_ERR_INTERNAL, "range tile passes disagree");
   if (idx_out && total > capacity)
@@ -1256,7 +1292,7 @@ tod_status run_lof_ties(const float* x, int64_t n, int64_t d, int32_t k, int64_t
   tod_status st = resolve_options(opts_in, &o);
   if (st != TOD_OK) return st;
   o.exclude_self = 1;
-  if (stats && stats->struct_size != sizeof(tod_stats))
+  if (!stats_size_ok(stats))
     return fail(TOD_ERR_INVALID_ARG, "tod_stats.struct_size does not match this library");
   if (!x) return fail(TOD_ERR_INVALID_ARG, "null input pointer");
   if (!lof_out) return fail(TOD_ERR_INVALID_ARG, "null LOF output");
@@ -1564,7 +1600,7 @@ tod_status tod_lof_ties(const float* x, int64_t n, int64_t d, int32_t k, int64_t
 tod_status tod_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, const tod_options* opts,
                     tod_stats* plan) {
   g_last_error.clear();
-  if (!plan || plan->struct_size != sizeof(tod_stats))
+  if (!plan || !stats_size_ok(plan))
     return fail(TOD_ERR_INVALID_ARG, "plan must point to a tod_stats with struct_size set");
   tod_options o;
   tod_status st = resolve_options(opts, &o);
@@ -1583,13 +1619,14 @@ tod_status tod_plan(int64_t nq, int64_t nr, int64_t d, int32_t k, const tod_opti
   plan->tile_launches = p.blocks;
   plan->reordered = p.order;
   plan->list_runs = p.runs;
+  if (plan->struct_size == sizeof(tod_stats)) plan->pruned_kind = tod::prune_block(p) ? p.prune : 0;
   return TOD_OK;
 }
 
 tod_status tod_plan_workspace(int64_t nq, int64_t nr, int64_t d, int32_t k, int32_t mode,
                               const tod_options* opts, size_t ws_bytes, tod_stats* plan) {
   g_last_error.clear();
-  if (!plan || plan->struct_size != sizeof(tod_stats))
+  if (!plan || !stats_size_ok(plan))
     return fail(TOD_ERR_INVALID_ARG, "plan must point to a tod_stats with struct_size set");
   if (mode < 0 || mode > 2) return fail(TOD_ERR_INVALID_ARG, "mode must be 0, 1 or 2");
   tod_options o;
@@ -1622,6 +1659,7 @@ tod_status tod_plan_workspace(int64_t nq, int64_t nr, int64_t d, int32_t k, int3
   plan->tile_launches = p.blocks;
   plan->reordered = p.order;
   plan->list_runs = p.runs;
+  if (plan->struct_size == sizeof(tod_stats)) plan->pruned_kind = tod::prune_block(p) ? p.prune : 0;
   return TOD_OK;
 }
 

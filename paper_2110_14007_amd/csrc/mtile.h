@@ -933,6 +933,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   [[maybe_unused]] int sg = -1, ubase = 0, par = 0;
   [[maybe_unused]] int64_t ucur = -1, uend = 0;
   [[maybe_unused]] bool uneed = false;
+  [[maybe_unused]] uint32_t nunits = 0;  // units this wave's queries needed
   [[maybe_unused]] const int nch = (nst + 63) >> 6, ch0 = st0 >> 6;
   [[maybe_unused]] uint64_t* const wneed = (uint64_t*)(qbase + W * NQ * kQCap * 64);  // [2][W]
   [[maybe_unused]] float nup[NQ];  // N_i and the limit's margin
@@ -1037,6 +1038,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     }
     const int bit = __builtin_ctzll(um);
     need = (om >> bit) & 1;
+    nunits += need ? 1 : 0;
     um &= um - 1;
     ucur = r_begin + (int64_t)uniform(ubase + bit) * UR;
     uneed = need;
@@ -1245,6 +1247,12 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
 #undef TOD_MT_FETCH
 #undef TOD_MT_PUT
   if (active) {
+    if constexpr (PR) {
+      // The pairs whose keys this wave computed (whole units of references).
+      if (lane == 0)
+        atomicAdd((unsigned long long*)&a.ctrl->uncertain[(group % kUncParts) * kUncStride],
+                  (unsigned long long)nunits * (UR * 32 * NQ));
+    }
     static_for<0, NQ>([&](auto U) __attribute__((always_inline)) {
       constexpr int u = decltype(U)::value;
       while (__ballot(cnt[u] > 0)) flush(U);

@@ -885,9 +885,13 @@ constexpr float kPieceCharge = 0.25f;
 
 __global__ void __launch_bounds__(kPlanThreads)
 plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, float l0, float fixed,
-                   const Ctrl* __restrict__ ctrl, int32_t* __restrict__ plan, int64_t rec_at) {
+                   const Ctrl* __restrict__ ctrl, int32_t* __restrict__ plan, int64_t rec_at,
+                   int32_t* __restrict__ ran) {
   if (ctrl->flat) {
-    if (threadIdx.x == 0) plan[0] = -1;
+    if (threadIdx.x == 0) {
+      plan[0] = -1;
+      *ran = 0;
+    }
     return;  // uniform
   }
   __shared__ float red[3][kPlanThreads / 64];
@@ -926,7 +930,10 @@ plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, f
   // the faster one (its sequence of stages is known): 6.1 ms against 6.6 at
   // 97,549 uniform rows of 26 (K' = 64), 27.1 against 29.4 at 269,454 of 65.
   if (total > kPruneWorth * (float)tiles * (float)stages) {
-    if (tid == 0) plan[0] = -1;
+    if (tid == 0) {
+      plan[0] = -1;
+      *ran = 0;
+    }
     return;  // uniform over the workgroup
   }
   auto pieces_of = [&](float est, float target) -> float {
@@ -1000,7 +1007,10 @@ plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, f
     }
     base += all;
   }
-  if (tid == 0) plan[0] = base;
+  if (tid == 0) {
+    plan[0] = base;
+    *ran = 1;
+  }
 }
 
 }  // namespace
@@ -1145,7 +1155,8 @@ hipError_t launch_plan(const Plan& p, const Args& a, int64_t q_begin, int64_t q_
                      tiles, p.prune, a.ctrl, a.plan + a.plan_tiles);
   hipLaunchKernelGGL(plan_pieces_kernel, dim3(1), dim3(kPlanThreads), 0, st, tiles, stages, slots,
                      cus, (int)a.plan_cap, 1024.0f * p.kprime / p.stage_rows,
-                     200.0f * p.kprime / p.stage_rows, a.ctrl, a.plan, a.plan_tiles);
+                     200.0f * p.kprime / p.stage_rows, a.ctrl, a.plan, a.plan_tiles,
+                     a.ran + q_begin / p.query_block);
   return hipGetLastError();
 }
 

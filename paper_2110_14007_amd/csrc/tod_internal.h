@@ -96,7 +96,7 @@ inline int tail_pieces(int64_t tw, int64_t slots, int64_t cus, int pmax, bool au
 struct Layout {
   size_t ctrl, mu64, mu32, colpart, xq_r, xq_q, hn_r, n64_q, rho_q, partial, ptail, worklist,
       fbtau, fbpart, fbidx, idx32, d64, lrd, kdist, perm, lab, oseed, cstart, bcnt, boff,
-      kstart, box32, sbox, xbox, substart, plan, total;
+      kstart, box32, sbox, xbox, substart, plan, ran, total;
   int32_t colpart_blocks;
 };
 
@@ -116,8 +116,8 @@ struct Ctrl {
   uint32_t bad_label;       // classifier: a reference label outside [0, n_classes)
   uint32_t flat;            // the pivots cannot tell the rows apart: plain scan, over evenly spaced
                             // seeds' groups (1) or in input order (2; order.hip)
-  // NWR: candidate pairs recomputed exactly, as kUncParts partial counts
-  // 128 bytes apart (the total is their sum).  Atomics on one address from
+  // NWR: candidate pairs recomputed exactly; kNN: pairs whose key the pruned scan
+  // computed.  As kUncParts partial counts 128 bytes apart (the total is their sum).  Atomics on one address from
   // every wave serialise: at 3 x 10^4 rows they took as long as the rest of
   // the verification.
   uint64_t uncertain[kUncParts * kUncStride];
@@ -189,6 +189,7 @@ struct Args {
   int32_t* plan;       // work plan of a launch (plan_words): extra pieces and the tiles' pieces
   int64_t plan_tiles;  // first word of the plan's per-tile records
   int64_t plan_cap;    // extra pieces the tail region holds
+  int32_t* ran;        // per query block: 1 if the pruned scan ran it, 0 if the plain one did
   int32_t* idx32;      // [nq x k] neighbour ids (LOF)
   double* d64;         // [nq x k] exact distances (LOF)
   double* lrd;         // [nq] LOF scratch

@@ -77,6 +77,9 @@ class tod_stats(ctypes.Structure):
         ("tail_parts", ctypes.c_int32),
         ("tail_rows", ctypes.c_int64),
         ("list_runs", ctypes.c_int32),
+        ("pruned_kind", ctypes.c_int32),
+        ("pruned_blocks", ctypes.c_int64),
+        ("pairs_scanned", ctypes.c_int64),
     ]
 
     def as_dict(self) -> dict:
@@ -204,7 +207,7 @@ def tod_plan_workspace(nq: int, nr: int, d: int, k: int, ws_bytes: int, mode: in
     _check(st, "tod_plan_workspace")
     return {"precision": PRECISION_NAMES[s.precision], "kprime": s.kprime,
             "ref_splits": s.ref_splits, "query_block": s.query_block, "blocks": s.blocks,
-            "reordered": s.reordered, "list_runs": s.list_runs}
+            "reordered": s.reordered, "list_runs": s.list_runs, "pruned_kind": s.pruned_kind}
 
 
 def tod_plan(nq: int, nr: int, d: int, k: int, opts=None) -> dict:
@@ -214,7 +217,8 @@ def tod_plan(nq: int, nr: int, d: int, k: int, opts=None) -> dict:
            "tod_plan")
     return {"precision": PRECISION_NAMES[s.precision], "kprime": s.kprime,
             "ref_splits": s.ref_splits, "query_block": s.query_block, "blocks": s.blocks,
-            "reordered": bool(s.reordered), "list_runs": s.list_runs}
+            "reordered": bool(s.reordered), "list_runs": s.list_runs,
+            "pruned_kind": s.pruned_kind}
 
 
 # ---------------------------------------------------------------------------

@@ -55,6 +55,19 @@ def test_struct_sizes_match(tod):
     assert e.value.status == tod.TOD_ERR_INVALID_ARG
 
 
+def test_first_layout_of_stats_accepted(tod):
+    # Callers built before pruned_kind was added pass a shorter struct.
+    s = tod.new_stats()
+    s.struct_size = tod.tod_stats.pruned_blocks.offset
+    assert s.struct_size == 136
+    s.pruned_kind = 7
+    lib = tod.raw_library()
+    assert lib.tod_plan(1000, 1000, 16, 10, None, ctypes.byref(s)) == 0
+    assert s.kprime >= 10 and s.pruned_kind == 7
+    s.struct_size = 128
+    assert lib.tod_plan(1000, 1000, 16, 10, None, ctypes.byref(s)) == tod.TOD_ERR_INVALID_ARG
+
+
 def test_status_strings(tod):
     assert tod.status_string(0) == "TOD_OK"
     assert tod.status_string(3) == "TOD_ERR_WORKSPACE"

@@ -87,9 +87,18 @@ def test_pruned_equals_plain(env, kind, n, d, k, opt):
     opt = dict(opt, reorder=1)
     got = tod.tod_knn_score(xd, k, tod.options(**opt), stats=st, return_lists=True)
     assert st.reordered
+    print("pruned_kind %d, blocks %d of %d, pairs %.3f" % (
+        st.pruned_kind, st.pruned_blocks, st.blocks, st.pairs_scanned / float(n) ** 2))
+    assert st.pruned_kind == (2 if d <= 16 else 1)
+    if kind == "clusters" and n > 4 * 4096:  # most pairs lie beyond the first 4,096 rows
+        assert st.pruned_blocks == st.blocks and st.pairs_scanned < 0.6 * n * n
+    if kind == "uniform" and d > 16:  # the plain scan takes over
+        assert st.pruned_blocks == 0 and st.pairs_scanned == n * n
     plain = dict(opt, reorder=-1)
     plain.pop("tail_parts", None)
-    ref = tod.tod_knn_score(xd, k, tod.options(**plain), return_lists=True)
+    pst = tod.new_stats()
+    ref = tod.tod_knn_score(xd, k, tod.options(**plain), stats=pst, return_lists=True)
+    assert pst.pruned_kind == 0 and pst.pruned_blocks == 0 and pst.pairs_scanned == n * n
     for u, v in zip(got, ref):
         assert torch.equal(u, v)
     rows = np.sort(rng.choice(n, 64, replace=False))
@@ -137,7 +146,7 @@ def test_extreme_magnitudes(env, kind, k):
 
 
 # A workspace without room for the tail region: the pruned scan's tiles stay uncut.
-@pytest.mark.parametrize("kind,share", [("clusters", 0.9), ("uniform", 0.9), ("clusters", 0.6)])
+@pytest.mark.parametrize("kind,share", [("clusters", 1.0), ("uniform", 1.0), ("clusters", 0.6)])
 def test_pruned_in_small_workspace(env, kind, share):
     torch, tod, oracle = env
     n, d, k = 150000, 24, 10
@@ -157,6 +166,54 @@ def test_pruned_in_small_workspace(env, kind, share):
                            score.data_ptr(), idx.data_ptr(), dist.data_ptr(), ctypes.byref(st))
     assert rc == 0, tod.last_error()
     assert st.tail_parts == 1 and st.reordered
+    assert st.pruned_blocks == (1 if kind == "clusters" and share == 1.0 else 0)
     ref = tod.tod_knn_score(xd, k, tod.options(reorder=-1), return_lists=True)
     for u, v in zip((score, idx, dist), ref):
         assert torch.equal(u, v)
+
+
+# The default route at the sizes where it begins (and, above 2^20 rows, with the local
+# splits of 4,096 rows), clustered and not.
+@pytest.mark.parametrize("kind", ["clusters", "uniform"])
+@pytest.mark.parametrize("n,d,k", [(60000, 17, 5), (65536, 6, 20), (131072, 8, 5),
+                                   ((1 << 20) + 37, 12, 5)])
+def test_default_route(env, kind, n, d, k):
+    torch, tod, oracle = env
+    x = data(kind, n, d, np.random.default_rng(n))
+    print("default route", kind, n, d, k, flush=True)
+    xd = torch.from_numpy(x).cuda()
+    st = tod.new_stats()
+    got = tod.tod_knn_score(xd, k, tod.options(), stats=st, return_lists=True)
+    print("blocks %d, pairs %.3f" % (st.pruned_blocks, st.pairs_scanned / float(n) ** 2))
+    assert st.reordered and st.pruned_kind == (2 if d <= 16 else 1)
+    if kind == "clusters":
+        assert st.pruned_blocks == 1 and st.pairs_scanned < 0.6 * n * n
+    ref = tod.tod_knn_score(xd, k, tod.options(reorder=-1), return_lists=True)
+    for u, v in zip(got, ref):
+        assert torch.equal(u, v)
+    rows = np.sort(np.random.default_rng(1).choice(n, 32, replace=False))
+    oidx, odist = oracle.knn_self(x, k, rows=rows)
+    compare_knn(x, x, rows, got[1].cpu().numpy()[rows], got[2].cpu().numpy()[rows], oidx, odist)
+
+
+def test_stats_of_the_scan_that_ran(env):
+    # Launches, tail and pairs are those of the scan that ran, block by block; a caller
+    # with the first layout of tod_stats gets the fields it has.
+    torch, tod, _ = env
+    x = torch.from_numpy(data("clusters", 70001, 20, np.random.default_rng(2))).cuda()
+    u = torch.from_numpy(data("uniform", 70001, 20, np.random.default_rng(2))).cuda()
+    st = tod.new_stats()
+    tod.tod_knn_score(x, 5, tod.options(), stats=st)
+    assert st.pruned_blocks == 1 and st.tile_launches == 1
+    assert st.tail_parts == 1 and st.tail_rows == 0
+    tod.tod_knn_score(u, 5, tod.options(), stats=st)
+    assert st.pruned_blocks == 0 and st.pairs_scanned == 70001 ** 2
+    assert st.tile_launches == (2 if 0 < st.tail_rows < 70001 else 1)
+    tod.tod_knn_score(x, 5, tod.options(query_block=16384), stats=st)
+    assert st.blocks == 5 and st.pruned_blocks == 5 and st.tile_launches == 5
+    old = tod.new_stats()
+    old.struct_size = tod.tod_stats.pruned_blocks.offset
+    old.pruned_kind, old.pruned_blocks, old.pairs_scanned = 7, 7, 7
+    tod.tod_knn_score(x, 5, tod.options(), stats=old)
+    assert old.kprime == st.kprime and old.tile_launches == 1
+    assert (old.pruned_kind, old.pruned_blocks, old.pairs_scanned) == (7, 7, 7)

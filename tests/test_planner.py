@@ -249,6 +249,23 @@ def test_two_runs_keep_their_splits(tod):
     assert tod.tod_plan(13000, 30000, 512, 100)["ref_splits"] == 2
 
 
+# Where the pruned scan begins by default, and the kind of its boxes.
+@pytest.mark.parametrize("d,rows,kind", [(6, 1 << 16, 2), (7, 1 << 17, 2), (8, 1 << 17, 2),
+                                         (9, 1 << 20, 2), (16, 1 << 20, 2), (17, 60000, 1),
+                                         (512, 60000, 1)])
+def test_prune_rule(tod, d, rows, kind):
+    for n, want in ((rows - 1, 0), (rows, kind)):
+        assert tod.tod_plan(n, n, d, 10, tod.options(exclude_self=True))["pruned_kind"] == want
+    for o in (dict(reorder=-1), dict(ref_splits=4), dict(precision="fp32")):
+        assert tod.tod_plan(rows, rows, d, 10, tod.options(exclude_self=True, **o))[
+            "pruned_kind"] == 0
+    # no room for the lists of cut scans: two rounds of workgroups and more
+    for n, want in ((131040, 0), (131072, kind)):
+        if n >= rows:
+            assert tod.tod_plan(n, n, d, 10, tod.options(exclude_self=True, tail_parts=1))[
+                "pruned_kind"] == want
+
+
 # The pivot distances lie over the partial lists: a block shrunk to the workspace
 # counts them once.
 @pytest.mark.parametrize("n,d,k,share", [(2797960, 98, 1, 0.95), (2797960, 98, 1, 0.9),
