@@ -95,19 +95,32 @@ typedef struct {
   float margin_scale;    /* >= 1: multiplies every error term of the certificate; 1 = default */
   int32_t force_fallback;/* debug: treat every row as uncertified (exact recomputation) */
   int32_t no_recheck;    /* debug: return the filter's shortlist order without verification */
-  int32_t reorder;       /* scan order of an X-against-X call (tod_knn with xq == xr, tod_knn_score,
-                          * tod_lof): 0 = planner, 1 = on, -1 = off.  On: the rows are grouped by
-                          * their nearest of G evenly spaced rows (G = 16, or for rows of at most
-                          * 16 elements one per 8192 rows, up to 1024) and every query block
-                          * first scans the references of its own group, so the filter's
-                          * thresholds tighten early.  Results are identical either way. */
+  int32_t reorder;       /* scan order and pruned scan of an X-against-X call (tod_knn with
+                          * xq == xr, tod_knn_score, tod_lof, tod_lof_ties, tod_abod, tod_cof)
+                          * through the register-list kernel (fp16 / bf16 filter, d <= 512, K' up
+                          * to 64, or 128 beyond 128 columns): 0 = planner, 1 = on, -1 = off.
+                          * Order: the rows are grouped by their nearest of G evenly spaced rows
+                          * (G = 16, or for rows of at most 16 elements one per 8192 rows, up to
+                          * 1024) and every query block first scans the references of its own
+                          * group, so the filter's thresholds tighten early.
+                          * Pruned scan: the order follows the nearest of 16 pivots and the
+                          * distance from it (d > 16), or a k-d tree over the columns, and
+                          * references whose box lies beyond a wave's K'-th distances are left
+                          * out.  Where the boxes rule too little out, the plain scan runs.
+                          * Planner: the order from 4096 rows on where the scan has one split;
+                          * the pruned scan, in query blocks of 8192 rows and more and with
+                          * ref_splits 0 or 1, from 60,000 rows on (d > 16), 65,536 (d <= 6),
+                          * 131,072 (d = 7, 8) or 2^20 (d = 9..16; one split).  On: from the first
+                          * row.  Results are identical either way. */
   int32_t score;         /* tod_score: the kNN outlier score of tod_knn_score, tod_knn_decision
                           * and tod_lof's knn_score_out */
   int32_t tail_parts;    /* fp16 / bf16 filter with one reference split: the workgroups of a
                           * query block's last, partly filled round of the GPU scan the
                           * references in this many parts on separate workgroups (their lists
                           * are merged before the recheck); 0 = planner, 1 = off, at most 8.
-                          * Results are identical either way. */
+                          * The pruned scan cuts its long scans by a plan of its own into the
+                          * same room; with 1 it cuts none, and runs only in blocks of 2^17 rows
+                          * and more.  Results are identical either way. */
 } tod_options;
 
 /* Plan and per-phase timings of one call (filled when a non-NULL pointer is
@@ -120,7 +133,7 @@ typedef struct {
                            * fields, which such a call leaves alone) */
   int32_t precision;      /* resolved tod_precision */
   int32_t kprime;         /* shortlist length K' */
-  int32_t ref_splits;     /* S */
+  int32_t ref_splits;     /* S (with pruned_kind > 0: of the blocks that the plain scan takes) */
   int64_t query_block;    /* B_q */
   int64_t blocks;         /* number of query blocks */
   int64_t rows_certified; /* rows whose shortlist passed the certificate */
@@ -130,12 +143,13 @@ typedef struct {
   float ms_prep, ms_tile, ms_recheck, ms_fallback, ms_score, ms_total;
                           /* ms_recheck includes the merge of the split lists, which runs
                            * inside the recheck kernel (there is no separate ms_merge) */
-  int32_t reordered;      /* 1 if the scan used the grouped row order (see tod_options.reorder) */
+  int32_t reordered;      /* 1 if the rows were put in the grouped order (see tod_options.reorder) */
   int64_t pairs_candidate; /* range queries (tod_nwr, tod_loci, tod_lof_ties): pairs the filter
                             * could not rule out of range */
   int64_t pairs_uncertain; /* range queries: candidates whose test needed the exact distance */
   int64_t pairs_in_range;  /* range queries: pairs within the threshold */
-  int32_t tail_parts;      /* parts the last partly filled round was scanned in (1: none) */
+  int32_t tail_parts;      /* parts the last partly filled round of a plain scan was scanned in
+                            * (1: none) */
   int64_t tail_rows;       /* query rows scanned in parts, summed over the blocks */
   int32_t list_runs;       /* 2 if each shortlist was built as two runs of K'/2 entries (the
                             * register-list tile over two pieces of the scan order: K' = 128

@@ -49,13 +49,16 @@ constexpr int64_t kUncutRows = 1 << 17;
 // 1.0 to 1.7 of five kinds of rows, of 4,096 0.41 to 1.25, of 8,192 0.45 to 0.95 where
 // the boxes rule rows out.
 constexpr int64_t kPruneMinBlock = 8192;
-// X against X from this many rows on runs the pruned scan.  Rows of more than 16 elements: below, more splits are the safer choice
-// (at 62,000 rows clustered ones take 0.51 to 0.68 of the two splits' time,
-// unclustered ones at most 1.04 of it; at 38,000 unclustered ones up to 1.56).
-// Shorter rows: boxes of columns rule less out the more columns there are, until
-// there are more of them.  At 75,000 to 95,000 rows of 4 to 6 columns the pruned
-// scan takes 0.43 to 0.97 of the plain one's time, of 8 up to 1.16, of 12 to 16 up
-// to 1.28 (270,000: 0.93 to 1.15); at 130,000 rows of 8 it takes 0.89 to 0.98.
+// X against X from this many rows on runs the pruned scan.  Time over that of the
+// splits without it:
+// - Rows of more than 16 elements, 62,000 of them: clustered ones 0.50 to 0.61,
+//   unclustered ones of 17 to 256 elements 0.79 to 1.02.  At 75,000 unclustered ones
+//   take 1.01 to 1.03 (the pivots, 40 to 60 us), at 200,000 1.00 to 1.02.  Below,
+//   clustered ones gain less, and at 38,000 unclustered ones took up to 1.56.
+// - Shorter rows: boxes of columns rule less out the more columns there are, until
+//   there are more rows.  At 75,000 to 95,000 rows of 4 to 6 columns 0.43 to 0.97, of
+//   8 up to 1.16, of 12 to 16 up to 1.28 (270,000: 0.93 to 1.15); at 130,000 rows of
+//   8 0.89 to 0.98.
 constexpr int64_t prune_rows(int64_t d) {
   return d <= 6 ? 65536 : d <= 8 ? 1 << 17 : d <= tod::kBoxDim ? 1 << 20 : 60000;
 }

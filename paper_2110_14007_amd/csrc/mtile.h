@@ -554,7 +554,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     const float e = max3f(v[12], v[13], v[14]);
     return Max2{max3f(a, b, c), max3f(d, e, v[15])};
   };
-  auto max16 = [&](const f32x16& v) {
+  [[maybe_unused]] auto max16 = [&](const f32x16& v) {
     const Max2 p = max16p(v);
     return max3f(p.f, p.g, p.g);
   };
@@ -860,8 +860,8 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // first (they give every query a threshold near its final one); the rest
   // follow from the start of the rows' group on (rows of at most 16 elements:
   // from their own place on), wrapping round.  A cut scan's piece takes every
-  // parts-th unit (without the boxes, a contiguous part of the order).  The pruned scan's unit is the box: a stage, or
-  // as many as make up 128 rows.
+  // parts-th unit (without the boxes, a contiguous part of the order).  The pruned
+  // scan's unit is the box: a stage, or as many as make up 128 rows.
   constexpr int UR = PR && TR < kUnitRows ? kUnitRows : TR;  // rows of a unit
   const int nst = (int)((r_end - r_begin + UR - 1) / UR);
   const int64_t p0 = q_begin + (int64_t)tile * (W * 32 * NQ);  // the tile's first query
@@ -1075,63 +1075,64 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     };
     // (Past the end the pipeline loads the first stage again; nothing reads it.)
     if constexpr (PR) {
-    [[maybe_unused]] bool n0, n1, n2;
-    int64_t t0 = next(n0);
-    const int64_t td = t0 < 0 ? r_begin : t0;
-    if constexpr (NBUF == 3) {
-      int64_t t1 = next(n1);
-      dl_issue(td, 0);
-      dl_issue(t1 < 0 ? td : t1, 1);
-      dl_barrier<kDlRows>();
-      for (int b = 0; t0 >= 0;) {
-        // Buffer (b + 2) % 3 was last read in the previous trip, before its barrier.
-        const int64_t t2 = next(n2);
-        const int b2 = b == 0 ? 2 : b - 1;
-        dl_body(t0, b, t2 < 0 ? td : t2, b2, n0);
+      [[maybe_unused]] bool n0, n1, n2;
+      int64_t t0 = next(n0);
+      const int64_t td = t0 < 0 ? r_begin : t0;
+      if constexpr (NBUF == 3) {
+        int64_t t1 = next(n1);
+        dl_issue(td, 0);
+        dl_issue(t1 < 0 ? td : t1, 1);
         dl_barrier<kDlRows>();
-        t0 = t1;
-        n0 = n1;
-        t1 = t2;
-        n1 = n2;
-        b = b == 2 ? 0 : b + 1;
-      }
-    } else {
-      dl_issue(td, 0);
-      dl_barrier<0>();
-      for (int b = 0; t0 >= 0; b ^= 1) {
-        // Buffer b ^ 1 was last read in the previous trip, before its barrier.
-        const int64_t t1 = next(n1);
-        dl_body(t0, b, t1 < 0 ? td : t1, b ^ 1, n0);
+        for (int b = 0; t0 >= 0;) {
+          // Buffer (b + 2) % 3 was last read in the previous trip, before its barrier.
+          const int64_t t2 = next(n2);
+          const int b2 = b == 0 ? 2 : b - 1;
+          dl_body(t0, b, t2 < 0 ? td : t2, b2, n0);
+          dl_barrier<kDlRows>();
+          t0 = t1;
+          n0 = n1;
+          t1 = t2;
+          n1 = n2;
+          b = b == 2 ? 0 : b + 1;
+        }
+      } else {
+        dl_issue(td, 0);
         dl_barrier<0>();
-        t0 = t1;
-        n0 = n1;
+        for (int b = 0; t0 >= 0; b ^= 1) {
+          // Buffer b ^ 1 was last read in the previous trip, before its barrier.
+          const int64_t t1 = next(n1);
+          dl_body(t0, b, t1 < 0 ? td : t1, b ^ 1, n0);
+          dl_barrier<0>();
+          t0 = t1;
+          n0 = n1;
+        }
       }
-    }
     } else {
-    if constexpr (NBUF == 3) {
-      dl_issue(t_of(0), 0);
-      dl_issue(t_of(1), 1);
-      dl_barrier<kDlRows>();
-      for (int it = 0; it < nscan; ++it) {
-        // Buffer (it + 2) % 3 was last read in trip it - 1, before its barrier.
-        dl_body(t_of(it), it % 3, t_of(it + 2), (it + 2) % 3, true);
+      if constexpr (NBUF == 3) {
+        dl_issue(t_of(0), 0);
+        dl_issue(t_of(1), 1);
         dl_barrier<kDlRows>();
-      }
-    } else {
-      dl_issue(t_of(0), 0);
-      dl_barrier<0>();
-      for (int it = 0; it < nscan; ++it) {
-        // Buffer (it + 1) & 1 was last read in trip it - 1, before its barrier.
-        dl_body(t_of(it), it & 1, t_of(it + 1), (it + 1) & 1, true);
+        for (int it = 0; it < nscan; ++it) {
+          // Buffer (it + 2) % 3 was last read in trip it - 1, before its barrier.
+          dl_body(t_of(it), it % 3, t_of(it + 2), (it + 2) % 3, true);
+          dl_barrier<kDlRows>();
+        }
+      } else {
+        dl_issue(t_of(0), 0);
         dl_barrier<0>();
+        for (int it = 0; it < nscan; ++it) {
+          // Buffer (it + 1) & 1 was last read in trip it - 1, before its barrier.
+          dl_body(t_of(it), it & 1, t_of(it + 1), (it + 1) & 1, true);
+          dl_barrier<0>();
+        }
       }
-    }
     }
     // No staging write may outlive the workgroup's LDS allocation.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else if constexpr (DLF) {
-    // Folded rows: 32 rows (1 KiB) an instruction, spread over the waves; a lane fetches the half its LDS place holds (swz).  Rows past the
-    // padded end repeat the last one and are never read back.
+    // Folded rows: 32 rows (1 KiB) an instruction, spread over the waves; a lane
+    // fetches the half its LDS place holds (swz).  Rows past the padded end repeat
+    // the last one and are never read back.
     constexpr int LPW = TR / 32 > W ? TR / 32 / W : 1;  // staging loads per wave and stage
     static_assert(TR / 32 <= W || (TR / 32) % W == 0, "staging loads spread evenly");
     const int lrow = lane >> 1;
@@ -1170,78 +1171,78 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
     // No staging write may outlive the workgroup's LDS allocation.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   } else {
-  if constexpr (PR) {
-  [[maybe_unused]] bool n0, n1, n2;
-  int64_t t0 = next(n0);
-  const int64_t td = t0 < 0 ? r_begin : t0;
-  TOD_MT_FETCH(td, st, sth)
-  TOD_MT_PUT(0, st, sth)
-  if constexpr (PF2) {
-    // Two stages per trip: each register set has a fixed role in straight-line
-    // code, so every wait is for the older set only, and the stage barrier
-    // (no release fence) leaves the newer set's loads in flight.
-    int64_t t1 = next(n1);
-    TOD_MT_FETCH((t1 < 0 ? td : t1), su, suh)
-    stage_barrier();
-    for (; t0 >= 0;) {
-      int64_t t2 = next(n2);
-      TOD_MT_FETCH((t2 < 0 ? td : t2), st, sth)
-      if (n0) stage_body(t0, 0);
-      TOD_MT_PUT(1, su, suh)
-      stage_barrier();
-      t0 = t2;
-      n0 = n2;
-      if (t1 < 0) break;
-      t2 = next(n2);
-      TOD_MT_FETCH((t2 < 0 ? td : t2), su, suh)
-      if (n1) stage_body(t1, 1);
+    if constexpr (PR) {
+      [[maybe_unused]] bool n0, n1, n2;
+      int64_t t0 = next(n0);
+      const int64_t td = t0 < 0 ? r_begin : t0;
+      TOD_MT_FETCH(td, st, sth)
       TOD_MT_PUT(0, st, sth)
-      stage_barrier();
-      t1 = t2;
-      n1 = n2;
-    }
-  } else {
-    __syncthreads();
-    for (int b = 0; t0 >= 0; b ^= 1) {
-      const int64_t t1 = next(n1);
-      TOD_MT_FETCH((t1 < 0 ? td : t1), st, sth)
-      if (n0) stage_body(t0, b);
-      TOD_MT_PUT(b ^ 1, st, sth)
-      __syncthreads();
-      t0 = t1;
-      n0 = n1;
-    }
-  }
+      if constexpr (PF2) {
+        // Two stages per trip: each register set has a fixed role in straight-line
+        // code, so every wait is for the older set only, and the stage barrier
+        // (no release fence) leaves the newer set's loads in flight.
+        int64_t t1 = next(n1);
+        TOD_MT_FETCH((t1 < 0 ? td : t1), su, suh)
+        stage_barrier();
+        for (; t0 >= 0;) {
+          int64_t t2 = next(n2);
+          TOD_MT_FETCH((t2 < 0 ? td : t2), st, sth)
+          if (n0) stage_body(t0, 0);
+          TOD_MT_PUT(1, su, suh)
+          stage_barrier();
+          t0 = t2;
+          n0 = n2;
+          if (t1 < 0) break;
+          t2 = next(n2);
+          TOD_MT_FETCH((t2 < 0 ? td : t2), su, suh)
+          if (n1) stage_body(t1, 1);
+          TOD_MT_PUT(0, st, sth)
+          stage_barrier();
+          t1 = t2;
+          n1 = n2;
+        }
+      } else {
+        __syncthreads();
+        for (int b = 0; t0 >= 0; b ^= 1) {
+          const int64_t t1 = next(n1);
+          TOD_MT_FETCH((t1 < 0 ? td : t1), st, sth)
+          if (n0) stage_body(t0, b);
+          TOD_MT_PUT(b ^ 1, st, sth)
+          __syncthreads();
+          t0 = t1;
+          n0 = n1;
+        }
+      }
     } else {
-  TOD_MT_FETCH(t_of(0), st, sth)
-  TOD_MT_PUT(0, st, sth)
-  if constexpr (PF2) {
-    // Two stages per trip: each register set has a fixed role in straight-line
-    // code, so every wait is for the older set only, and the stage barrier
-    // (no release fence) leaves the newer set's loads in flight.
-    TOD_MT_FETCH(t_of(1), su, suh)
-    stage_barrier();
-    for (int it = 0;;) {
-      TOD_MT_FETCH(t_of(it + 2), st, sth)
-      stage_body(t_of(it), 0);
-      TOD_MT_PUT(1, su, suh)
-      stage_barrier();
-      if (++it >= nscan) break;
-      TOD_MT_FETCH(t_of(it + 2), su, suh)
-      stage_body(t_of(it), 1);
+      TOD_MT_FETCH(t_of(0), st, sth)
       TOD_MT_PUT(0, st, sth)
-      stage_barrier();
-      if (++it >= nscan) break;
-    }
-  } else {
-    __syncthreads();
-    for (int it = 0; it < nscan; ++it) {
-      TOD_MT_FETCH(t_of(it + 1), st, sth)
-      stage_body(t_of(it), it & 1);
-      TOD_MT_PUT((it + 1) & 1, st, sth)
-      __syncthreads();
-    }
-  }
+      if constexpr (PF2) {
+        // Two stages per trip: each register set has a fixed role in straight-line
+        // code, so every wait is for the older set only, and the stage barrier
+        // (no release fence) leaves the newer set's loads in flight.
+        TOD_MT_FETCH(t_of(1), su, suh)
+        stage_barrier();
+        for (int it = 0;;) {
+          TOD_MT_FETCH(t_of(it + 2), st, sth)
+          stage_body(t_of(it), 0);
+          TOD_MT_PUT(1, su, suh)
+          stage_barrier();
+          if (++it >= nscan) break;
+          TOD_MT_FETCH(t_of(it + 2), su, suh)
+          stage_body(t_of(it), 1);
+          TOD_MT_PUT(0, st, sth)
+          stage_barrier();
+          if (++it >= nscan) break;
+        }
+      } else {
+        __syncthreads();
+        for (int it = 0; it < nscan; ++it) {
+          TOD_MT_FETCH(t_of(it + 1), st, sth)
+          stage_body(t_of(it), it & 1);
+          TOD_MT_PUT((it + 1) & 1, st, sth)
+          __syncthreads();
+        }
+      }
     }
   }
 #undef TOD_MT_FETCH

@@ -21,7 +21,10 @@ constexpr int stage_subs_base(int dpad) {
   return dpad == 16 ? 8 : (dpad == 32 ? 4 : (dpad == 64 ? 2 : 1));
 }
 constexpr int stage_subs(int dpad, bool fold, int r, bool pr) {
-  return pr && dpad == 16 ? 4 : fold && r <= 8 ? 16 : (dpad == 64 && !fold && r == 16) ? 4 : stage_subs_base(dpad);
+  return pr && dpad == 16                   ? 4
+         : fold && r <= 8                   ? 16
+         : (dpad == 64 && !fold && r == 16) ? 4
+                                            : stage_subs_base(dpad);
 }
 // Query columns per wave / 32: two groups sharing every A fragment for rows
 // of 512 elements with lists of up to 32 entries, whose 32-step MFMA chains

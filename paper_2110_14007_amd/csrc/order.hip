@@ -11,11 +11,13 @@
 // before it ranks and writes anything.
 //
 // Pruned scan.  On clustered rows most of the references cannot be among a
-// query's nearest: the boxes of sub-tiles and stages (distances to the seeds,
-// then called pivots) bound the distance between a wave's queries and a stage
-// from below, and the tile (mtile.h) skips what lies beyond the wave's worst
-// list entry.  At 10^6 rows of 64 in ten clusters the tile's 16 launches take 50
-// ms instead of 165, at 10^5 of 32 in five 1.2 instead of 2.2.
+// query's nearest: the boxes of sub-tiles and stages bound the distance between a
+// wave's queries and a stage from below, and the tile (mtile.h) skips what lies
+// beyond the wave's worst list entry.  At 10^6 rows of 64 in ten clusters the tile's
+// 16 launches take 50 ms instead of 165, at 10^5 of 32 in five 1.2 instead of 2.2.
+// The order then makes the boxes small: rows of more than 16 elements by the nearest
+// of kPivots pivots and the distance from it, shorter ones by a k-d tree.  Where the
+// boxes rule too little out, the plain scan runs (kFlatShare, kPruneWorth).
 #include "tod_internal.h"
 
 namespace tod {
@@ -133,11 +135,11 @@ __device__ __forceinline__ float scaled_elem(float x, float mu, double s) {
 // was 0.85 and more (boxes: 0.998 and more), on ten or five clusters 0.09 to 0.22
 // (0.14 to 0.38), on a curved sheet 0.16 to 0.22 (0.45 to 0.54).  From kFlatShare
 // on the call keeps to the plain scan over evenly spaced seeds, input order within
-// their groups (in several splits: over the rows in input order, whose splits are
-// all alike: 100,000 normal rows of 32 in blocks of 8,192 took 1.2 times as long in
-// eight pieces of the grouped order): pivots and distance bins made that 3 to 15 % slower there (their
+// their groups: pivots and distance bins made that 3 to 15 % slower there (their
 // order puts the outliers into tiles of their own, and a group's rows in the order
-// of their distance, not at random, fill the lists more often).
+// of their distance, not at random, fill the lists more often).  In several splits
+// it scans the rows in input order, whose splits are all alike (100,000 normal rows
+// of 32 in blocks of 8,192 took 1.2 times as long in eight pieces of the groups).
 constexpr int kFlatQueries = 32;
 constexpr float kFlatShare = 0.75f;
 constexpr int kSeedSamples = 512;
@@ -467,11 +469,12 @@ assign_kd_kernel(const float* __restrict__ x, int64_t n, int d, int levels,
   lab[row] = h - (1 << levels);
 }
 
-// Local splits: one workgroup per chunk of kKdChunk positions, down to 32 rows.  The rows' values sit in LDS as fp16 (scaled and centred
-// as for the quantisation; only the order matters), a key is (far flag, value,
-// local row).  Rows more than kKdFar times the chunk's mean squared distance
-// from its mean are flagged and end up last in the chunk, so that a few far
-// rows widen the boxes of the last sub-tiles only.
+// Local splits: one workgroup per chunk of kKdChunk positions, down to 32 rows.
+// The rows' values sit in LDS as fp16 (centred and scaled as for the quantisation;
+// only the order matters), a key is (far flag, value, local row).  Rows more than
+// kKdFar times the chunk's mean squared distance from its mean are flagged and end
+// up last in the chunk, so that a few far rows widen the boxes of the last sub-tiles
+// only.
 constexpr float kKdFar = 5.0f;
 
 template <int kKdChunk>
@@ -782,9 +785,9 @@ stage_box_kernel(const float* __restrict__ box32, int64_t subs, int64_t stages, 
 // estimated distance of the K'-th neighbour.  Pivots: the rows of a sub-tile
 // lie within twice its smallest pivot distance of each other; a sub-tile far
 // above both its neighbours (one that holds rows of two clusters) counts as the
-// larger of them, then the largest of the tile counts.  One wave per tile; at most kPlanSamples stages are tested, evenly
-// spaced.  The estimate only balances the pieces (at 10^5 rows of 32 and 10^6
-// of 64 it is within 1% of the stages scanned).
+// larger of them, then the largest of the tile counts.  One wave per tile; at most
+// kPlanSamples stages are tested, evenly spaced.  The estimate only balances the
+// pieces (at 10^5 rows of 32 and 10^6 of 64 it is within 1% of the stages scanned).
 constexpr int kPlanSamples = 2048;
 
 __global__ void __launch_bounds__(256)
@@ -884,9 +887,9 @@ constexpr float kSelCost = 1.7f;
 constexpr float kPieceCharge = 0.25f;
 
 __global__ void __launch_bounds__(kPlanThreads)
-plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, float l0, float fixed,
-                   const Ctrl* __restrict__ ctrl, int32_t* __restrict__ plan, int64_t rec_at,
-                   int32_t* __restrict__ ran) {
+plan_pieces_kernel(int64_t tiles, int64_t stages, int slots, int cus, int cap, float l0,
+                   float fixed, const Ctrl* __restrict__ ctrl, int32_t* __restrict__ plan,
+                   int64_t rec_at, int32_t* __restrict__ ran) {
   if (ctrl->flat) {
     if (threadIdx.x == 0) {
       plan[0] = -1;
@@ -1073,7 +1076,8 @@ hipError_t launch_order(const Plan& p, const Args& a, hipStream_t st) {
                                        (int)(sizeof(float) * kSeedFloats));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(pivot_seed_kernel, dim3(1), dim3(kSeedThreads), lds, st, a.xr, n, (int)p.d,
-                       m, tps, a.mu32, a.ctrl, p.scale_exp, !a.plan ? 0 : p.splits > 1 ? 2 : 1, a.pdist, srow);
+                       m, tps, a.mu32, a.ctrl, p.scale_exp, !a.plan ? 0 : p.splits > 1 ? 2 : 1,
+                       a.pdist, srow);
     hipLaunchKernelGGL(assign_pivot_kernel, dim3(ga), dim3(kAssignThreads),
                        sizeof(float) * kPivots * (size_t)p.d, st, a.xr, n, (int)p.d, a.mu32,
                        a.ctrl, p.scale_exp, srow, a.pdist, a.lab);
@@ -1137,7 +1141,9 @@ hipError_t launch_boxes(const Plan& p, const Args& a, hipStream_t st) {
     hipLaunchKernelGGL(column_box_kernel<__bf16>, dim3(gsub), bsub, 0, st, (const __bf16*)a.xq_r,
                        p.nr, subs, (int)p.d, p.dpad, a.box32, a.substart);
   }
-  const auto grid = [](int64_t boxes) { return dim3((unsigned)((boxes * 2 * kBoxDim + 255) / 256)); };
+  const auto grid = [](int64_t boxes) {
+    return dim3((unsigned)((boxes * 2 * kBoxDim + 255) / 256));
+  };
   const int64_t chunks = (stages + 63) / 64;
   hipLaunchKernelGGL(stage_box_kernel, grid(stages), dim3(256), 0, st, a.box32, subs, stages,
                      p.stage_rows / 32, a.ctrl, a.sbox);

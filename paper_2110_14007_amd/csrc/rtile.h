@@ -277,7 +277,7 @@ template <typename ET, int DPAD>
 hipError_t launch_range(const Plan& p, const Args& a, int64_t q_begin, int64_t q_rows, bool fill,
                         hipStream_t st) {
   using LY = mt::Layout<DPAD, false>;
-  const size_t lds = (size_t)2 * 32 * mt::stage_subs_base(DPAD) * LY::rowb + (size_t)2 * 32 * mt::stage_subs_base(DPAD) * sizeof(float);
+  const size_t lds = (size_t)2 * 32 * mt::stage_subs_base(DPAD) * (LY::rowb + sizeof(float));
   const auto kern = fill ? range_tile_kernel<ET, DPAD, true> : range_tile_kernel<ET, DPAD, false>;
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute((const void*)kern,

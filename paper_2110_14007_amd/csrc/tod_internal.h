@@ -117,9 +117,9 @@ struct Ctrl {
   uint32_t flat;            // the pivots cannot tell the rows apart: plain scan, over evenly spaced
                             // seeds' groups (1) or in input order (2; order.hip)
   // NWR: candidate pairs recomputed exactly; kNN: pairs whose key the pruned scan
-  // computed.  As kUncParts partial counts 128 bytes apart (the total is their sum).  Atomics on one address from
-  // every wave serialise: at 3 x 10^4 rows they took as long as the rest of
-  // the verification.
+  // computed.  As kUncParts partial counts 128 bytes apart (the total is their
+  // sum).  Atomics on one address from every wave serialise: at 3 x 10^4 rows they
+  // took as long as the rest of the range query's verification.
   uint64_t uncertain[kUncParts * kUncStride];
 };
 
