@@ -167,7 +167,9 @@ static int64_t auto_splits(const Plan& p, int64_t qb) {
   const bool whole = p.dpad_t > 0 && (p.precision == TOD_PREC_FP32 || p.dpad_t <= 128);
   const size_t lds =
       tile::lds_bytes(whole ? p.dpad_t : p.dpad, p.esize, (int)kp, w, whole);
-  const int64_t slots = kCus * (int64_t)(160 * 1024 / lds);
+  // (LDS is handed out in 1,280-byte pieces: three workgroups of 54,528 bytes do not
+  // fit in 160 KiB.)
+  const int64_t slots = kCus * (int64_t)(160 * 1024 / ((lds + 1279) / 1280 * 1280));
   const double row_us = p.precision == TOD_PREC_FP32 ? 0.0055 * (double)p.d
                                                      : 0.03 + 0.0008 * (double)p.d;
   const double fill = 8.6 * (double)kp / row_us;

@@ -233,7 +233,8 @@ def test_small_blocks_of_a_large_set(tod, d, qb):
     # the LDS-list kernel: K' = 128 and 256, fp32, rows beyond 512 columns
     (1500, 50000, 32, 100, "auto", 3, 32), (4000, 50000, 32, 100, "fp32", 3, 32),
     (2500, 50000, 16, 200, "auto", 2, 32), (3000, 40000, 32, 20, "fp32", 2, 128),
-    (3000, 30000, 700, 10, "auto", 1, 128), (1000, 30000, 700, 50, "auto", 1, 64),
+    (2012, 32000, 10, 1, "fp32", 2, 128), (5000, 50000, 6, 5, "fp32", 3, 128),
+    (2012, 50000, 14, 50, "fp32", 2, 64), (3000, 30000, 700, 10, "auto", 1, 128), (1000, 30000, 700, 50, "auto", 1, 64),
 ])
 def test_splits_fill_one_round(tod, nq, nr, d, k, prec, per_cu, rows):
     p = tod.tod_plan(nq, nr, d, k, tod.options(precision=prec))
