@@ -1008,6 +1008,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
         ubase = hs;
         um = __ballot(lane < hn && (hs + lane) % parts == offi);
         om = active ? um : 0;
+        nunits += (uint32_t)__builtin_popcountll(om);
         continue;
       }
       while (!sm) {
@@ -1034,11 +1035,11 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
       if (active && u < nst && (u < hs || u >= hs + hn) && (parts == 1 || u % parts == offi))
         ok = needs(a.sbox + (int64_t)u * (2 * kBoxDim), lim);
       om = __ballot(ok);
+      nunits += (uint32_t)__builtin_popcountll(om);
       um = any_wave(om);
     }
     const int bit = __builtin_ctzll(um);
     need = (om >> bit) & 1;
-    nunits += need ? 1 : 0;
     um &= um - 1;
     ucur = r_begin + (int64_t)uniform(ubase + bit) * UR;
     uneed = need;
