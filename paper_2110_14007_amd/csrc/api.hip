@@ -124,9 +124,11 @@ static int64_t long_splits(int64_t qb, int64_t nr) {
 
 // Reference splits for a query block of qb rows (Section 6 customised cdist
 // batching), by how many of the kernel's workgroups the GPU runs at once: at least
-// 8 K' references per split, and at most 64.  Every split fills its own K' list
-// per query, but while the GPU has idle compute units that runs beside the other
-// splits: what counts is the length of one wave's scan.
+// kSplitRows references per split, and at most 64.  Every split fills its own K'
+// list per query, but while the GPU has idle compute units that runs beside the
+// other splits: what counts is the length of one wave's scan.  (2,000 x 83 against
+// itself, K' = 64: 190 us in 16 splits, 278 in three, 221 in one with the tail split;
+// 1,000 x 16, K' = 128: 0.22 ms in 8 to 24, 0.64 in one.)
 //
 // Register-list kernel: as many splits as fit in one round.  A second round that is
 // not full costs more than it gives, also in place of one round that is a good half
@@ -147,9 +149,9 @@ static int64_t long_splits(int64_t qb, int64_t nr) {
 // 21, which no longer fit in one round; 14,000 take 4.0 in one, 5.3 in two or five;
 // 30,000 x 700, K' = 64: 20,000 take 24 ms in one, 17 in three.)
 static int64_t auto_splits(const Plan& p, int64_t qb) {
-  constexpr int64_t kCus = 256;
+  constexpr int64_t kCus = 256, kSplitRows = 128;
   const int64_t kp = p.kprime;
-  int64_t cap = p.nr / (8 * kp) > 1 ? p.nr / (8 * kp) : 1;
+  int64_t cap = p.nr / kSplitRows > 1 ? p.nr / kSplitRows : 1;
   if (cap > 64) cap = 64;
   int64_t s = 1;
   if (p.tile_kind == 1) {
