@@ -136,10 +136,9 @@ static int64_t long_splits(int64_t qb, int64_t nr) {
 // the next best 1.08 to 1.3 times as long, 7 splits 1.3 to 1.6; 30,000 queries 2,
 // three 1.25 to 1.4; 40,000 queries 1, two 1.11 to 1.32.  K' = 16 on 8 columns:
 // 10,000 queries 12 splits, six 1.25 to 1.4).  Two runs (K' = 128) already cut every
-// split in two.  With few pieces more rows fail the certificate, most in the
-// grouped order, whose pieces hold a row's neighbours together: X against X keeps
-// long_splits at least (40,000 x 200 in blocks of 8,192: 11.7 ms in 8 splits, 90 in
-// 4), other calls two (13,000 against 30,000 x 512, k = 100: 2.05 ms, in one 2.9).
+// split in two.  They take two splits at least where long_splits does: with two
+// lists of 64 more rows fail the certificate (13,000 against 30,000 x 512, k = 100:
+// 2.05 ms, in one split 2.9).
 //
 // LDS-list kernel (no tail split): the S with the shortest rounds, counting the
 // rows a wave could scan in the time it takes to fill its lists.  That time is
@@ -160,7 +159,7 @@ static int64_t auto_splits(const Plan& p, int64_t qb) {
                          mt::query_groups(p.dpad_t, p.fold, r);
     s = kCus * mt::tile_resident(p.dpad_t, p.fold, r) / ((qb + rows - 1) / rows) / p.runs;
     int64_t least = p.runs > 1 ? long_splits(qb, p.nr) : 1;
-    if (!p.self && least > 2) least = 2;
+    if (least > 2) least = 2;
     if (s < least) s = least;
     return s < cap ? s : cap;
   }

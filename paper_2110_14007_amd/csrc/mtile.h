@@ -365,6 +365,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   constexpr int kQCap = queue_slots<R, NQ>();
   constexpr int KC = LY::k16;
   constexpr bool kInterleave = NG == 1 && KC >= 16;
+  constexpr bool kRuns = DPAD >= 256 && !FOLD && R == 32;  // K' = 128 in two runs (a.runs)
   constexpr int kAhead = NQ > 1 ? 2 : 4;  // A fragments in flight ahead of the MFMA chain
   constexpr int ROWB = LY::rowb;
   constexpr bool SWZ = ROWB == 32;
@@ -866,7 +867,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   const int nst = (int)((r_end - r_begin + UR - 1) / UR);
   const int64_t p0 = q_begin + (int64_t)tile * (W * 32 * NQ);  // the tile's first query
   int st0 = 0, hs = 0, hn = 0;  // first stage of the rest; home stages [hs, hs + hn)
-  [[maybe_unused]] int nscan = nst, offi = 0;
+  [[maybe_unused]] int nscan = nst, offi = 0, step = 1;
   auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
   if constexpr (PR) {
     const int own = (int)(p0 / UR);
@@ -895,9 +896,18 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
         st0 = (int)((a.cstart[lo] - r_begin) / TR);
       }
     }
-    // Tail split: piece `split` of `parts` takes the stages [ib, ib + nscan) of
-    // the scan order.
-    if (pieces) {
+    // Two runs: the pieces are dealt the stages of the scan order in turn, so that
+    // the grouped order's near rows, which lie together, spread over the lists (in
+    // contiguous pieces, one list of 64 held most of a row's neighbours, and its end
+    // failed the certificate: 40,000 clustered rows of 200, k = 64, blocks of 8,192
+    // took 90 ms in 8 pieces, 11.6 in 16; dealt 4.6 in 4).
+    if (kRuns && a.runs > 1) {
+      step = parts;
+      nscan = split < nst ? (nst - split + parts - 1) / parts : 0;
+      st0 += split;
+    } else if (pieces) {
+      // Tail split: piece `split` of `parts` takes the stages [ib, ib + nscan) of
+      // the scan order.
       // (64-bit products: up to 128 pieces with two runs of 64 splits.)
       const int ib = (int)((int64_t)split * nst / parts);
       nscan = (int)((int64_t)(split + 1) * nst / parts) - ib;
@@ -908,9 +918,10 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
   // First row of the i-th stage scanned (i < nscan + 2 <= nst + 2; stages past
   // the last one wrap round and are loaded but never read).
   [[maybe_unused]] auto t_of = [&](int i) -> int64_t {
-    int s = st0 + i;
+    int s = st0 + (kRuns ? i * step : i);
     s = s >= nst ? s - nst : s;
     s = s >= nst ? s - nst : s;
+    if constexpr (kRuns) s = s < nst ? s : 0;  // (past the last one: any stage)
     return r_begin + (int64_t)s * TR;
   };
 
@@ -1223,7 +1234,7 @@ mtile_kernel(Args a, int64_t q_begin, int64_t q_rows) {
         // (no release fence) leaves the newer set's loads in flight.
         TOD_MT_FETCH(t_of(1), su, suh)
         stage_barrier();
-        for (int it = 0;;) {
+        for (int it = 0; it < nscan;) {  // (a piece of a small set can be empty)
           TOD_MT_FETCH(t_of(it + 2), st, sth)
           stage_body(t_of(it), 0);
           TOD_MT_PUT(1, su, suh)

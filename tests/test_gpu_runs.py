@@ -106,3 +106,37 @@ def test_few_references_per_run(env):
     say("short runs", st)
     assert st["list_runs"] == 2
     check_rows(env, x, k, res)
+
+
+# Small sets cut into more pieces than they have stages (some pieces are empty), and
+# clustered rows, whose neighbours lie together in the scan order.
+@pytest.mark.parametrize("n,d,k,splits,prec", [(300, 200, 60, 9, "bf16"), (170, 512, 40, 5, "bf16"),
+                                               (100, 140, 50, 3, "bf16"), (2000, 256, 100, 40, "fp16")])
+def test_pieces_of_small_sets(env, n, d, k, splits, prec):
+    torch, tod, oracle = env
+    x = lowrank(n, d, 77 + d)
+    say("pieces", n, d, k, splits)
+    xd = torch.from_numpy(x).cuda()
+    for opt in (dict(ref_splits=splits), dict(ref_splits=splits, reorder=1), dict()):
+        st = tod.new_stats()
+        _, idx, dist = tod.tod_knn_score(xd, k, tod.options(precision=prec, **opt), stats=st,
+                                         return_lists=True)
+        assert st.list_runs == 2
+        oidx, odist = oracle.knn_self(x, k)
+        compare_knn(x, x, np.arange(n), idx.cpu().numpy(), dist.cpu().numpy(), oidx, odist)
+
+
+def test_pieces_share_a_rows_neighbours(env):
+    torch, tod, _ = env
+    rng = np.random.default_rng(5)
+    c = 5.0 * rng.standard_normal((10, 200))
+    x = (c[rng.integers(0, 10, 20000)] + rng.standard_normal((20000, 200))).astype(np.float32)
+    xd = torch.from_numpy(x).cuda()
+    st = tod.new_stats()
+    _, idx, _ = tod.tod_knn_score(xd, 64, tod.options(query_block=8192), stats=st,
+                                  return_lists=True)
+    assert st.list_runs == 2
+    say("splits", st.ref_splits, "fallback rows", st.rows_fallback)
+    assert st.rows_fallback < 200  # contiguous pieces: most rows
+    _, ref, _ = tod.tod_knn_score(xd, 64, tod.options(precision="fp32"), return_lists=True)
+    assert torch.equal(idx, ref)

@@ -223,7 +223,7 @@ def test_small_blocks_of_a_large_set(tod, d, qb):
 
 # Splits fill one round of the kernel's workgroups and start no second one, where a
 # compute unit holds 1 to 3 of them (by the list's length, the row's and the
-# precision); two runs over the grouped order keep the pieces the certificate needs.
+# precision); two runs, whose splits have two pieces each, take two splits at least.
 @pytest.mark.parametrize("nq,nr,d,k,prec,per_cu,rows", [
     (10000, 50000, 8, 5, "auto", 1, 512), (10000, 50000, 16, 5, "auto", 3, 128),
     (10000, 50000, 32, 5, "auto", 2, 128), (10000, 50000, 64, 5, "auto", 3, 128),
@@ -243,10 +243,10 @@ def test_splits_fill_one_round(tod, nq, nr, d, k, prec, per_cu, rows):
     assert groups + -(-nq // rows) > 256 * per_cu * 0.9
 
 
-def test_two_runs_keep_their_splits(tod):
-    for qb, least in ((1024, 16), (8192, 8), (32768, 2)):
+def test_two_runs_take_two_splits(tod):
+    for qb, splits in ((1024, 16), (8192, 2), (32768, 2)):
         p = tod.tod_plan(40000, 40000, 200, 64, tod.options(query_block=qb, exclude_self=True))
-        assert p["list_runs"] == 2 and p["ref_splits"] >= least
+        assert p["list_runs"] == 2 and p["ref_splits"] == splits
     assert tod.tod_plan(13000, 30000, 512, 100)["ref_splits"] == 2
 
 
