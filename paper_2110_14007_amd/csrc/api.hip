@@ -45,9 +45,10 @@ constexpr int64_t kTailLists = 1 << 18;
 // Smallest query block of a pruned scan whose tiles cannot be cut (prune_block).
 constexpr int64_t kUncutRows = 1 << 17;
 // Smallest query block of a pruned scan (64 workgroups and their extra pieces).
-// 100,000 rows against themselves, time over that of the splits: blocks of 1,024
-// 1.0 to 1.7 of five kinds of rows, of 4,096 0.41 to 1.25, of 8,192 0.45 to 0.95 where
-// the boxes rule rows out.
+// 100,000 rows against themselves, time over that of the splits, clustered rows of 32
+// and 200, a mixture of 64, uniform rows of 6, normal ones of 32: blocks of 1,024
+// 1.01, 0.68, 1.65, 2.1, 2.9; of 4,096 0.64, 0.41, 0.92, 1.24, 1.6; of 8,192 0.55,
+// 0.45, 0.71, 0.94, 1.03.
 constexpr int64_t kPruneMinBlock = 8192;
 // X against X from this many rows on runs the pruned scan.  Time over that of the
 // splits without it:
